@@ -310,13 +310,14 @@ __device__ __forceinline__ int order_bucket(uint64_t l) {
 // Dispatch order of the work items.  Items that hold a full kItemSplats
 // splats run first (in tile order: dispatch slot i < F, F the number of such
 // items, is tile t's full item i - (items[t] - t)); then every tile's last
-// item, longest first: tile_order lists the tiles by the length of that
-// item, counting-sorted in buckets of 32 splats.  Heavy items start early,
+// item, longest first: tile_order holds (tile, its list's first and end
+// position, its number of items), what a raster workgroup needs to begin, by
+// the length of that item, counting-sorted in buckets of 32 splats.  Heavy items start early,
 // so the launch ends on short ones instead of waiting for a late heavy one.
 // Only the order of execution changes (within a bucket it varies from run
 // to run): every item writes the same outputs.
 __global__ __launch_bounds__(kTileScanThreads) void tile_scan_single(uint32_t* tile_start, int64_t total_tiles,
-                                                                     uint32_t* items, uint32_t* tile_order,
+                                                                     uint32_t* items, uint4* tile_order,
                                                                      DevFlags* flags, int64_t capacity) {
   __shared__ uint32_t sh[16];
   __shared__ uint32_t bucket[kOrderBuckets];
@@ -377,9 +378,13 @@ __global__ __launch_bounds__(kTileScanThreads) void tile_scan_single(uint32_t* t
     }
   }
   __syncthreads();  // the starts of every tile and the bucket offsets are in place
-  for (int64_t t = threadIdx.x; t < total_tiles; t += kTileScanThreads)
-    tile_order[atomicAdd(&bucket[order_bucket(capped_len(tile_start[t], tile_start[t + 1], cap))], 1u)] =
-        static_cast<uint32_t>(t);
+  for (int64_t t = threadIdx.x; t < total_tiles; t += kTileScanThreads) {
+    const uint64_t a = tile_start[t], l = capped_len(a, tile_start[t + 1], cap);
+    const uint64_t a0 = a < cap ? a : cap;
+    tile_order[atomicAdd(&bucket[order_bucket(l)], 1u)] =
+        make_uint4(static_cast<uint32_t>(t), static_cast<uint32_t>(a0), static_cast<uint32_t>(a0 + l),
+                   static_cast<uint32_t>(l == 0 ? 1 : (l + kItemSplats - 1) / kItemSplats));
+  }
 }
 
 // Exclusive scan (in place) of the per-(view, block) rectangle sums, in
@@ -454,7 +459,7 @@ hipError_t launch_bin(const Layout& L, void* ws, void* pairs, int64_t capacity, 
   if ((e = hipGetLastError()) != hipSuccess) return e;
   // tile starts, overflow flags and raster work items in one workgroup
   tile_scan_single<<<1, kTileScanThreads, 0, st>>>(tstart, L.total_tiles, items,
-                                                   at<uint32_t>(ws, L.off_torder), flags, capacity);
+                                                   at<uint4>(ws, L.off_torder), flags, capacity);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   // Gaussian-major offsets of the blocks (the counting pass summed each
   // block's rectangle sizes); the scatter pass writes goff
