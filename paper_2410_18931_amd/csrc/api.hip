@@ -1,5 +1,6 @@
 // C-ABI entry points of the WSR library (declared in include/wsr.h): argument
 // checks, workspace layout, and the launch sequence of each step.
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 
@@ -20,18 +21,44 @@ int32_t to_status(hipError_t e) { return e == hipSuccess ? WSR_OK : WSR_ERR_HIP;
 
 }  // namespace
 
+// Gaussians per binning block: the fewest, 256 to 2,048, whose count matrix
+// (blocks x tiles) stays within kBinSmall entries.  With few Gaussians or tiles
+// a block's serial expansion is the whole pass and wants to be short (4,096
+// Gaussians at 128 x 128: 43 us of binning passes in blocks of 2,048, 10 us in
+// blocks of 256); with many the matrix's traffic grows with the blocks (1 M
+// Gaussians at 1080p: the stage takes 175 us in blocks of 2,048, 206 us in
+// blocks of 1,024, 177 us in blocks of 4,096).  200 k Gaussians at 1280 x 720
+// and 300 k at 1001 x 747 take 49 and 55 us with the line here, 54 and 56 us
+// with it at half and 53 and 67 us at twice as many entries.
+constexpr int kBinChunkMin = 256, kBinChunkMax = 2048;
+constexpr int64_t kBinSmall = 1 << 20;
+
+int64_t blocks_of(int64_t n, int64_t chunk) { return n > 0 ? (n + chunk - 1) / chunk : 1; }
+
 bool make_layout(int64_t n, const wsr_camera* cams, int32_t nv, int32_t tile, Layout* L, DevCamera* dc) {
   if (n < 0 || n > 0xffffffffLL || !cams || nv < 1 || nv > WSR_MAX_VIEWS || !valid_tile(tile)) return false;
   *L = Layout();
   L->n = n;
   L->nv = nv;
   L->tile = tile;
-  L->nblk = static_cast<int32_t>(n > 0 ? (n + kBinChunk - 1) / kBinChunk : 1);
-  int64_t tiles = 0, pixels = 0, hist = 0;
+  int64_t tiles = 0, pixels = 0;
   for (int v = 0; v < nv; ++v) {
     const wsr_camera& c = cams[v];
     if (c.width < 1 || c.height < 1 || c.width > 32767 || c.height > 32767) return false;
     if (!(c.fx > 0.f) || !(c.fy > 0.f)) return false;
+    tiles += static_cast<int64_t>((c.width + tile - 1) / tile) * ((c.height + tile - 1) / tile);
+  }
+  if (tiles > 0x7fffffffLL) return false;
+  L->bin_chunk = kBinChunkMin;
+  while (L->bin_chunk < kBinChunkMax && blocks_of(n, L->bin_chunk) * tiles > kBinSmall) L->bin_chunk *= 2;
+  L->nblk = static_cast<int32_t>(blocks_of(n, L->bin_chunk));
+  // the largest matrix of any chunk for up to n Gaussians, so that a workspace
+  // never holds fewer Gaussians than it was sized for
+  const int64_t hist_room = std::max(blocks_of(n, kBinChunkMax) * tiles, std::min(blocks_of(n, kBinChunkMin) * tiles, kBinSmall));
+  int64_t hist = 0;
+  tiles = 0;
+  for (int v = 0; v < nv; ++v) {
+    const wsr_camera& c = cams[v];
     const int tx = (c.width + tile - 1) / tile, ty = (c.height + tile - 1) / tile;
     if (tx > L->max_tiles_x) L->max_tiles_x = tx;
     if (ty > L->max_tiles_y) L->max_tiles_y = ty;
@@ -53,7 +80,6 @@ bool make_layout(int64_t n, const wsr_camera* cams, int32_t nv, int32_t tile, La
     pixels += static_cast<int64_t>(c.width) * c.height;
     hist += static_cast<int64_t>(tx) * ty * L->nblk;
   }
-  if (tiles > 0x7fffffffLL) return false;
   L->total_tiles = tiles;
   L->total_pixels = pixels;
   L->hist_len = hist;
@@ -66,8 +92,8 @@ bool make_layout(int64_t n, const wsr_camera* cams, int32_t nv, int32_t tile, La
   L->off_queue = off;    off = align256(off + sizeof(uint32_t) * 2);
   L->off_rec = off;      off = align256(off + sizeof(DevSplat) * slots);
   L->off_rect = off;     off = align256(off + sizeof(uint2) * slots);
-  L->off_hist = off;     off = align256(off + sizeof(uint32_t) * (hist + 1));
-  L->off_scan = off;     off = align256(off + sizeof(uint32_t) * L->scan_parts);
+  L->off_hist = off;     off = align256(off + sizeof(uint32_t) * (hist_room + 1));
+  L->off_scan = off;     off = align256(off + sizeof(uint32_t) * nv * blocks_of(n, kBinChunkMin));
   L->off_goff = off;     off = align256(off + sizeof(uint32_t) * (slots + 1));
   L->off_grad2d = off;   off = align256(off + sizeof(float) * 9 * slots);
   L->off_tstart = off;   off = align256(off + sizeof(uint32_t) * (tiles + 1));

@@ -3,9 +3,9 @@
 // the step that replaces the per-tile depth sort of 3DGS (Sec. 4.1).
 //
 // A counting sort by tile built from LDS histograms, with no global atomics:
-//   1. bin_pass<count>: block (b, z, v) takes Gaussians [b*kBinChunk, ...) of
+//   1. bin_pass<count>: block (b, z, v) takes Gaussians [b*chunk, ...) of
 //      view v and counts their (tile, Gaussian) pairs into an LDS histogram
-//      of the tile rows of chunk z, written contiguously as row b of the
+//      of the tile rows of band z, written contiguously as row b of the
 //      block-major count matrix M[v][b][tile].
 //   2. column_scan_wide: each tile's column of M becomes exclusive prefixes
 //      over the blocks, and the tile's total; tile_scan_single scans the
@@ -13,13 +13,12 @@
 //   3. bin_pass<scatter>: the same blocks re-expand their pairs and place
 //      each pair's entry (Gaussian id, Gaussian-major slot, see below) at
 //      tile_start[t] + M[v][b][t] + the pair's stable rank in the block.
-// Pairs are expanded load-balanced: per round of 256 Gaussians a block-wide
-// scan of the pair counts lets every thread take every 256th pair, so one
-// huge splat does not serialise on one thread.  The scatter is stable: every
-// tile's list holds its Gaussian ids in increasing order, whatever the
-// timing of the run.  Eq. 7 does not need an order, but the float sums of
-// the raster stages follow the list order, so a fixed order makes the whole
-// path reproducible bit for bit.
+// A wave expands its Gaussians 64 at a time: a wave-wide scan of their pair
+// counts, then 64 pairs per step, one per lane, so one huge splat does not
+// serialise on one thread.  The scatter is stable: every tile's list holds its
+// Gaussian ids in increasing order, whatever the timing of the run.  Eq. 7
+// does not need an order, but the float sums of the raster stages follow the
+// list order, so a fixed order makes the whole path reproducible bit for bit.
 //
 // The same step also lays out the backward's per-pair scratch: every
 // (view, Gaussian) gets a contiguous range of "Gaussian-major" slots, one per
@@ -35,30 +34,25 @@ namespace wsr {
 namespace {
 
 constexpr int kBinThreads = 256;
+constexpr int kBinWaves = kBinThreads / kWave;
 
-// Exclusive scan of one value per thread over a 256-thread block.  Returns
-// the exclusive prefix; *total receives the block sum.  `sh` needs 4 words.
-__device__ inline uint32_t block_scan_256(uint32_t v, uint32_t* sh, uint32_t* total) {
-  const int lane = threadIdx.x & (kWave - 1);
-  const int wv = threadIdx.x / kWave;
-  uint32_t inc = v;
-#pragma unroll
-  for (int d = 1; d < kWave; d <<= 1) {
-    const uint32_t o = __shfl_up(inc, d, kWave);
-    if (lane >= d) inc += o;
-  }
-  if (lane == kWave - 1) sh[wv] = inc;
-  __syncthreads();
-  uint32_t base = 0, tot = 0;
-#pragma unroll
-  for (int k = 0; k < kBinThreads / kWave; ++k) {
-    const uint32_t s = sh[k];
-    if (k < wv) base += s;
-    tot += s;
-  }
-  __syncthreads();
-  *total = tot;
-  return base + inc - v;
+// Inclusive sum over the lanes of a wave, in registers (DPP row shifts, then
+// the row totals broadcast on).
+__device__ __forceinline__ uint32_t wave_scan(uint32_t x) {
+  x += __builtin_amdgcn_update_dpp(0u, x, 0x111, 0xf, 0xf, false);  // row_shr:1
+  x += __builtin_amdgcn_update_dpp(0u, x, 0x112, 0xf, 0xf, false);  // row_shr:2
+  x += __builtin_amdgcn_update_dpp(0u, x, 0x114, 0xf, 0xf, false);  // row_shr:4
+  x += __builtin_amdgcn_update_dpp(0u, x, 0x118, 0xf, 0xf, false);  // row_shr:8
+  x += __builtin_amdgcn_update_dpp(0u, x, 0x142, 0xa, 0xf, false);  // row_bcast:15 to rows 1, 3
+  x += __builtin_amdgcn_update_dpp(0u, x, 0x143, 0xc, 0xf, false);  // row_bcast:31 to rows 2, 3
+  return x;
+}
+
+// LDS writes of this wave before, LDS reads of this wave after.
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 struct BinArgs {
@@ -71,17 +65,135 @@ struct BinArgs {
   int64_t capacity;
   int32_t rows_per_chunk;
   int32_t nblk;                // blocks per view
+  int32_t chunk;               // Gaussians per block, a multiple of kBinThreads
   uint32_t* parts;             // per (view, block): sum of the rectangle sizes, then its exclusive scan
   uint32_t* goff;              // Gaussian-major first slot of every (view, Gaussian)
 };
 
+// One Gaussian's tile rectangle, whole and cut to a band of tile rows.
+struct BinRect {
+  uint32_t x0, w, y0, count;  // cut to the band: columns [x0, x0 + w), first row, tiles
+  uint32_t full;              // tiles of the whole rectangle
+  uint32_t first;             // row-major index of tile (0, 0) in it: y0 w + x0 of the whole, negated
+};
+
+__device__ __forceinline__ BinRect bin_rect(uint2 r, int ry0, int ry1) {
+  BinRect b;
+  const uint32_t x1 = r.x >> 16, y0 = r.y & 0xffffu, y1 = r.y >> 16;
+  b.x0 = r.x & 0xffffu;
+  b.w = x1 > b.x0 ? x1 - b.x0 : 0u;
+  const int yl = max(static_cast<int>(y0), ry0), yh = min(static_cast<int>(y1), ry1);
+  b.y0 = static_cast<uint32_t>(yl);
+  b.count = yh > yl ? b.w * static_cast<uint32_t>(yh - yl) : 0u;
+  b.full = y1 > y0 ? b.w * (y1 - y0) : 0u;
+  b.first = 0u - (y0 * b.w + b.x0);
+  return b;
+}
+
+// The pairs of a wave's 64 Gaussians (one rectangle per lane), in
+// Gaussian-major order (a Gaussian's tiles row-major), 64 per step:
+// f(valid, owner lane, tx, ty, w).  A pair's owner is the last Gaussian whose
+// first pair is not behind it: the owners that begin in the step mark their
+// place in `mark` (64 words of LDS of this wave's own).
+template <typename F>
+__device__ __forceinline__ void expand_pairs(const BinRect& r, uint32_t* mark, int lane, F&& f) {
+  const uint32_t inc = wave_scan(r.count), off = inc - r.count;
+  const uint32_t total = __builtin_amdgcn_readlane(inc, kWave - 1);
+  const uint32_t span = r.x0 | (r.w << 16);
+  int last = 0;  // owner of the previous step's last pair
+  for (uint32_t p0 = 0; p0 < total; p0 += kWave) {
+    mark[lane] = kWave;
+    wave_lds_fence();
+    if (r.count > 0 && off >= p0 && off - p0 < kWave) mark[off - p0] = lane;
+    wave_lds_fence();
+    const int here = static_cast<int>(mark[lane]);
+    const uint64_t begun = __ballot(here < kWave) & ((2ull << lane) - 1ull);
+    const int from = __shfl(here, begun ? 63 - __clzll(begun) : 0, kWave);
+    const int owner = begun ? from : last;
+    last = __builtin_amdgcn_readlane(owner, kWave - 1);
+    const uint32_t p = p0 + lane;
+    const bool valid = p < total;
+    const uint32_t local = p - __shfl(off, owner, kWave);
+    const uint32_t sp = __shfl(span, owner, kWave), y0 = __shfl(r.y0, owner, kWave);
+    const uint32_t w = max(sp >> 16, 1u);
+    // local / w: at most 4,096 rows, so the float quotient is within one of it
+    int q = static_cast<int>(static_cast<float>(local) * __builtin_amdgcn_rcpf(static_cast<float>(w)));
+    int rem = static_cast<int>(local) - q * static_cast<int>(w);
+    if (rem < 0) {
+      --q;
+      rem += static_cast<int>(w);
+    } else if (rem >= static_cast<int>(w)) {
+      ++q;
+      rem -= static_cast<int>(w);
+    }
+    f(valid, owner, (sp & 0xffffu) + static_cast<uint32_t>(rem), y0 + static_cast<uint32_t>(q), w);
+  }
+}
+
+// Rectangles into a band's difference array d (rows x tiles_x, one word per
+// tile): four corners each, whose two-dimensional prefix sums are the number of
+// rectangles over every tile.  `one` is the unit to add (1, or 1 << 16 for a
+// count kept in the upper half of the words; the sums are linear, so the
+// halves do not mix in the end).
+__device__ __forceinline__ void add_corners(uint32_t* d, const BinRect& r, int ry0, int ry1, int tiles_x, uint32_t one) {
+  if (r.count == 0) return;
+  const int top = (static_cast<int>(r.y0) - ry0) * tiles_x;
+  const int bottom = top + static_cast<int>(r.count / r.w) * tiles_x;  // first row below
+  const bool below = bottom < (ry1 - ry0) * tiles_x;
+  const int left = static_cast<int>(r.x0), right = static_cast<int>(r.x0 + r.w);
+  atomicAdd(&d[top + left], one);
+  if (right < tiles_x) atomicAdd(&d[top + right], 0u - one);
+  if (below) {
+    atomicAdd(&d[bottom + left], 0u - one);
+    if (right < tiles_x) atomicAdd(&d[bottom + right], one);
+  }
+}
+
+// The prefix sums of NW difference arrays (contiguous, `tiles` words each), in
+// place, by the whole workgroup: down the columns, then along the rows.
+template <int NW>
+__device__ __forceinline__ void prefix_counts(uint32_t* d, int tiles, int tiles_x, int wv, int lane) {
+  const int rows = tiles / tiles_x;
+  __syncthreads();
+  for (int c = threadIdx.x; c < NW * tiles_x; c += kBinThreads) {
+    uint32_t* col = d + c / tiles_x * tiles + c % tiles_x;
+    uint32_t run = 0;
+    for (int r = 0; r < rows; ++r) {
+      run += col[r * tiles_x];
+      col[r * tiles_x] = run;
+    }
+  }
+  __syncthreads();
+  for (int k = wv; k < NW * rows; k += kBinWaves) {
+    uint32_t* row = d + k / rows * tiles + k % rows * tiles_x;
+    uint32_t carry = 0;
+    for (int x0 = 0; x0 < tiles_x; x0 += kWave) {
+      const int x = x0 + lane;
+      const uint32_t inc = wave_scan(x < tiles_x ? row[x] : 0u);
+      if (x < tiles_x) row[x] = carry + inc;
+      carry += __builtin_amdgcn_readlane(inc, kWave - 1);
+    }
+  }
+  __syncthreads();
+}
+
+// Counting and scattering pass.  Every wave takes a quarter of the block's
+// Gaussians.  Counting needs no pairs: a rectangle adds its four corners to a
+// difference array in LDS, whose prefix sums are the counts.  The scatter
+// counts each wave's pairs per tile in the same way, which gives each wave
+// cursors of its own (16 bits per wave and tile, behind the block's 32-bit
+// base), and then expands and places the pairs with no barrier between the
+// waves.  (Before, every pair was expanded to be counted, its Gaussian found by
+// binary search in LDS, and the waves took turns at one cursor per tile, four
+// barriers per 256 pairs: at 1 M Gaussians / 1080p counting 43 instead of
+// 18 us, scattering 130 as before, at 200 k / 720p 21 and 45 instead of 7 and
+// 23 us.)
+constexpr int kTags = 1024;
+
 template <bool SCATTER>
 __global__ __launch_bounds__(kBinThreads) void bin_pass(BinArgs a) {
   extern __shared__ uint32_t lds[];
-  __shared__ uint32_t s_off[kBinThreads];
-  __shared__ uint32_t s_x0[kBinThreads], s_w[kBinThreads], s_y0[kBinThreads];
-  __shared__ uint32_t s_gadj[kBinThreads];  // scatter: goff - (y0 w + x0), mod 2^32
-  __shared__ uint32_t s_scan[4];
+  __shared__ uint32_t s_full[kBinWaves];
 
   const int b = blockIdx.x, z = blockIdx.y, v = blockIdx.z;
   const DevCamera& cam = a.cams[v];
@@ -91,122 +203,95 @@ __global__ __launch_bounds__(kBinThreads) void bin_pass(BinArgs a) {
   if (ry0 >= cam.tiles_y) return;
   const int ry1 = min(ry0 + a.rows_per_chunk, cam.tiles_y);
   const int chunk_tiles = (ry1 - ry0) * tiles_x;
-  const int t0 = ry0 * tiles_x;  // first tile (view-local) of the chunk
+  const int t0 = ry0 * tiles_x;  // first tile (view-local) of the band
   uint32_t* row = a.hist + cam.hist_base + static_cast<int64_t>(b) * tiles_v + t0;
+  const int lane = threadIdx.x & (kWave - 1), wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
 
-  for (int t = threadIdx.x; t < chunk_tiles; t += kBinThreads)
-    lds[t] = SCATTER ? a.tile_start[cam.tile_base + t0 + t] + row[t] : 0u;
+  // count: one word per tile; scatter: two words of two counts each, then
+  // cursors, and the block's base per tile
+  constexpr int NW = SCATTER ? 2 : 1;
+  uint32_t* counts = lds;
+  uint32_t* base = lds + NW * chunk_tiles;
+  for (int t = threadIdx.x; t < NW * chunk_tiles; t += kBinThreads) counts[t] = 0u;
+  if (SCATTER)
+    for (int t = threadIdx.x; t < chunk_tiles; t += kBinThreads) base[t] = a.tile_start[cam.tile_base + t0 + t] + row[t];
   __syncthreads();
 
-  const int64_t g0 = static_cast<int64_t>(b) * kBinChunk;
-  const int64_t g1 = min(g0 + kBinChunk, a.n);
+  const int64_t g0 = static_cast<int64_t>(b) * a.chunk + static_cast<int64_t>(wv) * (a.chunk / kBinWaves);
+  const int64_t g1 = min(g0 + a.chunk / kBinWaves, a.n);
   const uint2* rect = a.rect + static_cast<int64_t>(v) * a.n;
-  const int lane = threadIdx.x & (kWave - 1), wv = threadIdx.x / kWave;
-  // bits of a chunk-local tile index
-  const int tbits = chunk_tiles > 1 ? 32 - __clz(static_cast<uint32_t>(chunk_tiles - 1)) : 1;
   const int64_t part = static_cast<int64_t>(v) * a.nblk + b;
-  // running Gaussian-major offset of this block (counting pass: from 0, for
-  // the block's sum; scatter pass: from the block's scanned offset)
-  uint32_t gcarry = SCATTER ? a.parts[part] : 0u;
-  for (int64_t base = g0; base < g1; base += kBinThreads) {
-    const int64_t i = base + threadIdx.x;
-    uint32_t cnt = 0, x0 = 0, w = 0, y0 = 0;
-    if (i < g1) {
-      const uint2 r = rect[i];
-      x0 = r.x & 0xffffu;
-      const uint32_t x1 = r.x >> 16;
-      const int yl = max(static_cast<int>(r.y & 0xffffu), ry0);
-      const int yh = min(static_cast<int>(r.y >> 16), ry1);
-      w = x1 > x0 ? x1 - x0 : 0u;
-      if (yh > yl && w > 0) {
-        cnt = w * static_cast<uint32_t>(yh - yl);
-        y0 = static_cast<uint32_t>(yl);
-      }
-    }
-    if (SCATTER || z == 0) {
-      // this (view, Gaussian)'s whole rectangle: its run of Gaussian-major
-      // slots (counting pass, first band: the block's sum; scatter pass:
-      // goff, stored by the first band, and each pair's slot)
-      uint32_t full = 0, gadj = 0;
-      if (i < g1) {
-        const uint2 r = rect[i];
-        const uint32_t rx0 = r.x & 0xffffu, rx1 = r.x >> 16, ry0r = r.y & 0xffffu, ry1r = r.y >> 16;
-        full = (rx1 > rx0 && ry1r > ry0r) ? (rx1 - rx0) * (ry1r - ry0r) : 0u;
-        gadj = 0u - (ry0r * (rx1 - rx0) + rx0);
-      }
-      uint32_t ftot;
-      const uint32_t fex = block_scan_256(full, s_scan, &ftot);
-      if (SCATTER) {
-        s_gadj[threadIdx.x] = gcarry + fex + gadj;  // slot of tile (tx, ty): this + ty w + tx
-        if (z == 0 && i < g1) a.goff[static_cast<int64_t>(v) * a.n + i] = gcarry + fex;
-      }
-      gcarry += ftot;
-    }
-    uint32_t total;
-    const uint32_t off = block_scan_256(cnt, s_scan, &total);
-    s_off[threadIdx.x] = off;
-    s_x0[threadIdx.x] = x0;
-    s_w[threadIdx.x] = w;
-    s_y0[threadIdx.x] = y0;
-    __syncthreads();
-    // pairs p0 .. p0 + 255 of the round, in Gaussian-major order (a
-    // Gaussian's tiles row-major), one per thread
-    for (uint32_t p0 = 0; p0 < total; p0 += kBinThreads) {
-      const uint32_t p = p0 + threadIdx.x;
-      const bool valid = p < total;
-      uint32_t t = 0, pslot = 0;
-      int lo = 0;
-      if (valid) {
-        // largest g with s_off[g] <= p (it has a non-zero count)
-        int hi = kBinThreads - 1;
-        while (lo < hi) {
-          const int mid = (lo + hi + 1) >> 1;
-          if (s_off[mid] <= p) lo = mid; else hi = mid - 1;
-        }
-        const uint32_t local = p - s_off[lo];
-        const uint32_t ww = s_w[lo];
-        const uint32_t ty = s_y0[lo] + local / ww;
-        const uint32_t tx = s_x0[lo] + local % ww;
-        t = (ty - ry0) * tiles_x + tx;
-        if (SCATTER) pslot = s_gadj[lo] + ty * ww + tx;  // the pair's Gaussian-major slot
-      }
-      if (!SCATTER) {
-        if (valid) atomicAdd(&lds[t], 1u);
-        continue;
-      }
-      // Stable rank: the lanes of this wave holding the same tile are those
-      // that agree with this lane on every bit of the tile index (one ballot
-      // per bit); among them, lower lanes hold earlier pairs.
-      const uint64_t vmask = __ballot(valid);
-      uint64_t peers = vmask;
-      for (int k = 0; k < tbits; ++k) {
-        const bool bit = ((t >> k) & 1u) != 0u;
-        const uint64_t bm = __ballot(valid && bit);
-        if (bm != 0ull && bm != vmask) peers &= bit ? bm : ~bm;
-      }
-      const uint32_t rank = static_cast<uint32_t>(__popcll(peers & ((1ull << lane) - 1ull)));
-      const uint32_t grp = static_cast<uint32_t>(__popcll(peers));
-      const bool last = (peers >> lane) == 1ull;  // highest lane of its group
-      // The waves place their pairs in turn (wave order is pair order): each
-      // reads its tiles' cursors, and the last lane of a group advances its
-      // tile's cursor past the group.
-#pragma unroll
-      for (int turn = 0; turn < kBinThreads / kWave; ++turn) {
-        if (wv == turn && valid) {
-          const uint32_t start = lds[t];
-          const uint32_t pos = start + rank;
-          if (pos < a.capacity)
-            a.ent[pos] = make_uint2(static_cast<uint32_t>(base + lo), pslot);
-          if (last) lds[t] = start + grp;
-        }
-        __syncthreads();
-      }
-    }
-    __syncthreads();
+
+  uint32_t full = 0;
+  for (int64_t i = g0 + lane; i < g1; i += kWave) {
+    const BinRect r = bin_rect(rect[i], ry0, ry1);
+    full += r.full;
+    add_corners(counts + (SCATTER ? (wv >> 1) * chunk_tiles : 0), r, ry0, ry1, tiles_x,
+                SCATTER ? 1u << (16 * (wv & 1)) : 1u);
   }
-  if (!SCATTER) {
-    for (int t = threadIdx.x; t < chunk_tiles; t += kBinThreads) row[t] = lds[t];
-    if (z == 0 && threadIdx.x == 0) a.parts[part] = gcarry;
+  // (view, block) rectangle sums, for the Gaussian-major slots
+  const uint32_t fsum = wave_scan(full);
+  if (lane == kWave - 1) s_full[wv] = fsum;
+  prefix_counts<NW>(counts, chunk_tiles, tiles_x, wv, lane);
+  if constexpr (!SCATTER) {
+    for (int t = threadIdx.x; t < chunk_tiles; t += kBinThreads) row[t] = counts[t];
+    if (z == 0 && threadIdx.x == 0) a.parts[part] = s_full[0] + s_full[1] + s_full[2] + s_full[3];
+  } else {
+    __shared__ uint32_t s_mark[kBinWaves][kWave];
+    __shared__ uint8_t s_tag[kBinWaves][kTags];
+    uint32_t* mark = s_mark[wv];
+    uint8_t* tag = s_tag[wv];
+    // counts of waves 0 to 3 -> their first places
+    for (int t = threadIdx.x; t < chunk_tiles; t += kBinThreads) {
+      const uint32_t c0 = counts[t] & 0xffffu, c1 = counts[t] >> 16, c2 = counts[chunk_tiles + t] & 0xffffu;
+      counts[t] = c0 << 16;
+      counts[chunk_tiles + t] = (c0 + c1) | ((c0 + c1 + c2) << 16);
+    }
+    __syncthreads();
+    uint32_t gcarry = a.parts[part];  // running Gaussian-major offset
+    for (int w = 0; w < wv; ++w) gcarry += s_full[w];
+    uint16_t* cursor = reinterpret_cast<uint16_t*>(counts + (wv >> 1) * chunk_tiles) + (wv & 1);  // tile t's: [2 t]
+    auto load = [&](int64_t i) { return i < g1 ? rect[i] : make_uint2(0u, 0u); };
+    uint2 next = load(g0 + lane);
+    for (int64_t g = g0; g < g1; g += kWave) {
+      const BinRect r = bin_rect(next, ry0, ry1);
+      next = load(g + kWave + lane);
+      const uint32_t finc = wave_scan(r.full);
+      const uint32_t goff = gcarry + finc - r.full;
+      gcarry += __builtin_amdgcn_readlane(finc, kWave - 1);
+      if (z == 0 && g + lane < g1) a.goff[static_cast<int64_t>(v) * a.n + g + lane] = goff;
+      const uint32_t gadj = goff + r.first;  // slot of tile (tx, ty): this + ty w + tx
+      expand_pairs(r, mark, lane, [&](bool valid, int owner, uint32_t tx, uint32_t ty, uint32_t w) {
+        const uint32_t t = valid ? (ty - ry0) * tiles_x + tx : 0u;
+        const uint32_t slot = __shfl(gadj, owner, kWave) + ty * w + tx;
+        // Stable rank among the step's pairs of the same tile, where lower
+        // lanes hold earlier pairs.  Every lane leaves its number at its
+        // tile's tag; those that find another there share the tag, as a rule
+        // the tile, and their groups are formed one by one.
+        if (valid) tag[t % kTags] = static_cast<uint8_t>(lane);
+        wave_lds_fence();
+        const uint32_t at = valid ? base[t] + cursor[2 * t] : 0u;
+        uint64_t left = __ballot(valid && tag[t % kTags] != lane);
+        uint32_t rank = 0;
+        bool last = true;
+        while (left) {
+          const uint32_t tl = __builtin_amdgcn_readlane(t, __ffsll(static_cast<long long>(left)) - 1);
+          const uint64_t same = __ballot(valid && t == tl);
+          if (t == tl) {
+            rank = static_cast<uint32_t>(__popcll(same & ((1ull << lane) - 1ull)));
+            last = (same >> lane) == 1ull;
+          }
+          left &= ~same;
+        }
+        if (valid) {
+          const uint32_t pos = at + rank;
+          if (pos < a.capacity) a.ent[pos] = make_uint2(static_cast<uint32_t>(g) + owner, slot);
+          // the highest lane of its group moves the wave's cursor past the group
+          if (last) cursor[2 * t] = static_cast<uint16_t>(at + rank + 1u - base[t]);
+        }
+        wave_lds_fence();
+      });
+    }
   }
 }
 
@@ -440,10 +525,12 @@ hipError_t launch_bin(const Layout& L, void* ws, void* pairs, int64_t capacity, 
   a.nblk = L.nblk;
   a.parts = parts;
   a.goff = goff;
-  // whole tile rows per LDS chunk, at most kTileChunk tiles, and at least
-  // kBinBands chunks of rows: each block then expands only the pairs of its
-  // band, and the four times more blocks keep more of the chip busy (binning
-  // 0.254 -> 0.214 ms at 1 M Gaussians / 1080p)
+  a.chunk = L.bin_chunk;
+  // whole tile rows per band, at most kTileChunk tiles, and at least kBinBands
+  // bands: each block then expands only the pairs of its band, and the four
+  // times more blocks keep more of the chip busy (the stage at 1 M Gaussians /
+  // 1080p, 300 k / 1001 x 747 and 16 views: 175, 55 and 1,398 us with 4 bands,
+  // 171, 54 and 1,405 us with 6, 178, 59 and 1,433 us with 8)
   constexpr int kBinBands = 4;
   if (kTileChunk / L.max_tiles_x < 1) return hipErrorInvalidValue;
   a.rows_per_chunk = min(kTileChunk / L.max_tiles_x, (L.max_tiles_y + kBinBands - 1) / kBinBands);
@@ -464,7 +551,7 @@ hipError_t launch_bin(const Layout& L, void* ws, void* pairs, int64_t capacity, 
   // Gaussian-major offsets of the blocks (the counting pass summed each
   // block's rectangle sizes); the scatter pass writes goff
   scan_parts<<<1, 1024, 0, st>>>(parts, static_cast<int64_t>(L.nv) * L.nblk, goff + L.n * L.nv);
-  bin_pass<true><<<grid, kBinThreads, lds, st>>>(a);
+  bin_pass<true><<<grid, kBinThreads, 3 * lds, st>>>(a);
   return hipGetLastError();
 }
 

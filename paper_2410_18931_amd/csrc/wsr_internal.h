@@ -10,9 +10,7 @@
 namespace wsr {
 
 constexpr int kWave = 64;
-constexpr int kBinChunk = 2048;       // Gaussians per binning block
-constexpr int kTileChunk = 14336;     // tiles per binning LDS histogram (56 KB + static < 64 KB)
-constexpr int kRasterBatch = 256;     // splats staged in LDS per batch
+constexpr int kTileChunk = 4864;      // tiles per binning band (12 bytes of LDS each in the scatter: 57 KB)
 constexpr int kItemSplats = 2048;     // a tile's list is split into raster work items of at most this many
 constexpr int kProjBlock = 256;
 
@@ -101,13 +99,14 @@ struct Layout {
   int64_t n = 0;
   int32_t nv = 0;
   int32_t tile = 16;
-  int32_t nblk = 1;          // binning blocks per view = ceil(n / kBinChunk)
+  int32_t bin_chunk = 256;   // Gaussians per binning block
+  int32_t nblk = 1;          // binning blocks per view = ceil(n / bin_chunk)
   int32_t max_tiles_x = 1;
   int32_t max_tiles_y = 1;
   int64_t total_tiles = 0;
   int64_t total_pixels = 0;
   int64_t hist_len = 0;      // entries of the count matrix (without the trailing total)
-  int64_t scan_parts = 0;
+  int64_t scan_parts = 0;    // binning blocks of all views
   size_t off_cams = 0, off_flags = 0, off_rec = 0, off_rect = 0, off_hist = 0, off_scan = 0,
          off_goff = 0, off_grad2d = 0, off_tstart = 0, off_tilepart = 0, off_gpart = 0, off_items = 0, off_torder = 0, off_acc = 0,
          off_oit = 0, off_acclog = 0, off_du2d = 0,
