@@ -90,6 +90,7 @@ bool make_layout(int64_t n, const wsr_camera* cams, int32_t nv, int32_t tile, La
   L->off_cams = off;     off = align256(off + sizeof(DevCamera) * WSR_MAX_VIEWS);
   L->off_flags = off;    off = align256(off + sizeof(DevFlags));
   L->off_queue = off;    off = align256(off + sizeof(uint32_t) * 2);
+  L->off_sortq = off;    off = align256(off + sizeof(uint32_t) * 4);
   L->off_rec = off;      off = align256(off + sizeof(DevSplat) * slots);
   L->off_rect = off;     off = align256(off + sizeof(uint2) * slots);
   L->off_hist = off;     off = align256(off + sizeof(uint32_t) * (hist_room + 1));

@@ -111,6 +111,7 @@ struct Layout {
          off_goff = 0, off_grad2d = 0, off_tstart = 0, off_tilepart = 0, off_gpart = 0, off_items = 0, off_torder = 0, off_acc = 0,
          off_oit = 0, off_acclog = 0, off_du2d = 0,
          off_queue = 0;  // work-item counters of the persistent raster launches (forward, backward)
+  size_t off_sortq = 0;   // the sorted baseline's queue of tiles with long lists: numbers and claims
   int64_t gpart_blocks = 0;
   size_t bytes = 0;
 };
