@@ -68,6 +68,7 @@ struct BinArgs {
   int32_t chunk;               // Gaussians per block, a multiple of kBinThreads
   uint32_t* parts;             // per (view, block): sum of the rectangle sizes, then its exclusive scan
   uint32_t* goff;              // Gaussian-major first slot of every (view, Gaussian)
+  int bands;                 // bands of tile rows per view
 };
 
 // One Gaussian's tile rectangle, whole and cut to a band of tile rows.
@@ -186,7 +187,7 @@ __device__ __forceinline__ void prefix_counts(uint32_t* d, int tiles, int tiles_
 // waves.  (Before, every pair was expanded to be counted, its Gaussian found by
 // binary search in LDS, and the waves took turns at one cursor per tile, four
 // barriers per 256 pairs: at 1 M Gaussians / 1080p counting 43 instead of
-// 18 us, scattering 130 as before, at 200 k / 720p 21 and 45 instead of 7 and
+// 18 us, scattering 130 us as before, at 200 k / 720p 21 and 45 instead of 7 and
 // 23 us.)
 constexpr int kTags = 1024;
 
@@ -195,7 +196,14 @@ __global__ __launch_bounds__(kBinThreads) void bin_pass(BinArgs a) {
   extern __shared__ uint32_t lds[];
   __shared__ uint32_t s_full[kBinWaves];
 
-  const int b = blockIdx.x, z = blockIdx.y, v = blockIdx.z;
+  // Workgroups go round the eight XCDs in turn.  Each XCD takes a contiguous
+  // eighth of a view's blocks, band by band, so that the parts of a tile's list
+  // that lie side by side are written through one L2 (the stage at 1 M
+  // Gaussians / 1080p 175 -> 166 us, 16 views 1,398 -> 1,273 us; with a part of
+  // the bands per XCD instead, whose loads differ, 203 and 1,475 us).
+  const uint32_t per = (a.nblk + 7) / 8, k = blockIdx.x / 8;
+  const int b = blockIdx.x % 8 * per + k % per, z = k / per % a.bands, v = k / per / a.bands;
+  if (b >= a.nblk) return;
   const DevCamera& cam = a.cams[v];
   const int tiles_x = cam.tiles_x;
   const int tiles_v = cam.tiles_x * cam.tiles_y;
@@ -527,17 +535,19 @@ hipError_t launch_bin(const Layout& L, void* ws, void* pairs, int64_t capacity, 
   a.goff = goff;
   a.chunk = L.bin_chunk;
   // whole tile rows per band, at most kTileChunk tiles, and at least kBinBands
-  // bands: each block then expands only the pairs of its band, and the four
-  // times more blocks keep more of the chip busy (the stage at 1 M Gaussians /
-  // 1080p, 300 k / 1001 x 747 and 16 views: 175, 55 and 1,398 us with 4 bands,
-  // 171, 54 and 1,405 us with 6, 178, 59 and 1,433 us with 8)
-  constexpr int kBinBands = 4;
+  // bands: each block then expands only the pairs of its band, and the more
+  // blocks keep more of the chip busy (the stage at 1 M Gaussians / 1080p,
+  // 200 k / 720p, 300 k / 1001 x 747 and 16 views: 166, 48, 52 and 1,273 us with
+  // 4 bands, 161, 46, 52 and 1,267 us with 6, 161, 47, 58 and 1,264 us with 8,
+  // 165, 52, 62 and 1,352 us with 12)
+  constexpr int kBinBands = 6;
   if (kTileChunk / L.max_tiles_x < 1) return hipErrorInvalidValue;
   a.rows_per_chunk = min(kTileChunk / L.max_tiles_x, (L.max_tiles_y + kBinBands - 1) / kBinBands);
   if (a.rows_per_chunk < 1) a.rows_per_chunk = 1;
   const int nchunks = (L.max_tiles_y + a.rows_per_chunk - 1) / a.rows_per_chunk;
   const size_t lds = static_cast<size_t>(a.rows_per_chunk) * L.max_tiles_x * sizeof(uint32_t);
-  const dim3 grid(static_cast<unsigned>(L.nblk), static_cast<unsigned>(nchunks), static_cast<unsigned>(L.nv));
+  a.bands = nchunks;
+  const unsigned grid = static_cast<unsigned>(static_cast<int64_t>((L.nblk + 7) / 8 * 8) * nchunks * L.nv);
 
   hipError_t e;
   bin_pass<false><<<grid, kBinThreads, lds, st>>>(a);
