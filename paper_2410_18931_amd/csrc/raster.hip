@@ -1456,7 +1456,7 @@ __device__ __forceinline__ void sort_list(SortShared<CAP, NB, TH>& sh, const uin
         uint32_t pos = k0;
         for (uint32_t k = k0; k < k1; k += 2) {
           const uint64_t x = sh.keys[k], y = sh.keys[min(k + 1, k1 - 1)];
-          pos += (x < key ? 1u : 0u) + (y < key & k + 1 < k1 ? 1u : 0u);
+          pos += (x < key ? 1u : 0u) + ((y < key && k + 1 < k1) ? 1u : 0u);
         }
         place[r] = pos;
       }

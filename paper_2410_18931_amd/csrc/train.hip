@@ -12,12 +12,26 @@
 //   dmean/dx = (G*dS/du + 2 x G*dS/dSxx + y G*dS/dSxy) / P
 // (the window is symmetric, so its adjoint is the same zero-padded filter).
 //
-// Two passes over 16 x 16 pixel tiles with a 5-pixel halo staged in LDS and
-// the separable filter applied along rows, then columns:
-//   loss_pass1: the five windowed statistics -> map, the three derivative
-//               maps (to the workspace) and the tile's share of the loss;
-//   loss_pass2: the three derivative maps filtered again -> dL/dx.
-// The tile shares are summed in FP64 in a fixed order (loss_finalize).
+// Two passes, the separable filter applied along rows, then columns:
+//   pass1: the five windowed statistics -> map, the three derivative maps (to
+//          the workspace) and each workgroup's (or wave's) share of the loss;
+//   pass2: the three derivative maps filtered again -> dL/dx.
+// The shares are summed in FP64 in a fixed order (loss_finalize).
+//
+// Small images are cut into 16 x 16 pixel tiles, one workgroup per tile and
+// channel, staged with a 5-pixel halo in LDS (loss_pass1, loss_pass2): many
+// short workgroups, but every row is filtered 1.6 times and the filtered rows
+// pass through LDS again.  Large ones are cut into strips 64 pixels wide and
+// 34 rows high, one wave per channel and one column per lane, which walk down
+// the strip (loss_strip_pass1, loss_strip_pass2): a row with its halo is staged
+// in LDS and filtered along the row once (1.3 times with the halo rows), and
+// the last eleven filtered rows stay in registers for the filter along the
+// column.  Fused multiply-adds are most of what either issues; a strip's rows
+// are a serial chain of about 0.6 us each, so it needs enough pixels to give
+// every SIMD some waves.  Both passes with the loss's sum, us, tiles and strips:
+// 17 x 9 and 65 x 33 14 / 49, 640 x 360 34 / 54, three views of 400 x 300
+// 43 / 55, 960 x 540 60 / 54, 1280 x 720 90 / 69, sixteen views of 400 x 300
+// 171 / 102, 1920 x 1080 209 / 108, four of them 719 / 400.
 #include <cmath>
 #include <type_traits>
 #include <mutex>
@@ -39,13 +53,20 @@ namespace {
 constexpr int kLT = 16;               // output tile edge
 constexpr int kHalo = 5;              // window radius
 constexpr int kLE = kLT + 2 * kHalo;  // staged edge (26)
+constexpr int kTaps = 2 * kHalo + 1;
+constexpr int kStrip = kWave;         // output columns of a strip
+constexpr int kStripRows = 34;        // output rows: 44 staged rows, four rounds of eleven (23 rows: 130 us at
+                                      // 1920 x 1080 instead of 108, 45 rows: 116)
+constexpr int kStaged = kStrip + 2 * kHalo;
+constexpr int kStripThreads = 3 * kWave;  // one wave per channel
+constexpr int kAhead = 3;             // rows loaded ahead (2: 116 us at 1920 x 1080, 3: 108, 4: 118, 5: 129)
 constexpr int kLossViewsPerLaunch = 16;
 constexpr float kC1 = 0.01f * 0.01f;
 constexpr float kC2 = 0.03f * 0.03f;
 
 // Views of one launch, passed by value: sizes, first pixel of each view in
-// the concatenated images, first 16x16 loss tile of each view (global over
-// all views) and the loss scale 1 / (P_v V) of each view.
+// the concatenated images, first tile (16 x 16, or a strip) of each view and
+// the loss scale 1 / (P_v V) of each view.
 struct LossViews {
   int32_t nv;
   int32_t tile0;  // first tile of this launch (global index)
@@ -61,7 +82,9 @@ struct LossViews {
 struct LossArgs {
   const float* img;
   const float* target;
-  float* dmaps;           // [3][channel][pixel] derivative maps
+  float* dmaps;           // [3][channel][pixel] derivative maps (tiles)
+  float2* dmap2;          // the same for strips: [channel][pixel] dS/du and dS/dSxx
+  float* dmap1;           // and [channel][pixel] dS/dSxy
   double* part;           // [tile * 3 + channel] loss shares
   float* dL;
   int64_t total_pixels;
@@ -248,7 +271,239 @@ __global__ __launch_bounds__(256) void loss_pass2(LossArgs a, LossViews lv) {
   a.dL[3 * pix + ch] = sc * ((1.f - a.lambda) * sgn - a.lambda * dmean);
 }
 
-// Sum of the tile shares in a fixed order: one block, strided partial sums,
+// Where a strip lies, and the lane's part of a staged row: its own pixel at
+// the strip's left edge - 5 + lane and, for the first ten lanes, the one 64
+// further on.  A pixel outside the view reads a pixel of it and counts as zero.
+struct Strip {
+  int v, x0, y0;
+  int width, height;
+  int64_t pix_base;
+  int c0, c1;        // columns read
+  bool in0, in1;
+};
+
+__device__ __forceinline__ Strip loss_strip(const LossViews& lv, int t, int lane) {
+  Strip w;
+  w.v = 0;
+  while (w.v + 1 < lv.nv && lv.tile_base[w.v + 1] <= t) ++w.v;
+  const int local = t - lv.tile_base[w.v];
+  w.x0 = local % lv.tiles_x[w.v] * kStrip;
+  w.y0 = local / lv.tiles_x[w.v] * kStripRows;
+  w.width = lv.width[w.v];
+  w.height = lv.height[w.v];
+  w.pix_base = lv.pix_base[w.v];
+  const int a = w.x0 - kHalo + lane, b = a + kWave;
+  w.in0 = a >= 0 && a < w.width;
+  w.in1 = lane < 2 * kHalo && b < w.width;
+  w.c0 = min(max(a, 0), w.width - 1);
+  w.c1 = min(b, w.width - 1);
+  return w;
+}
+
+// The taps in vector registers (an operand from a scalar register halves the
+// rate of a fused multiply-add), six values since the window is symmetric.
+struct Taps {
+  float g[kHalo + 1];
+  __device__ __forceinline__ float operator[](int k) const { return g[k <= kHalo ? k : 2 * kHalo - k]; }
+};
+__device__ __forceinline__ Taps load_taps(const LossViews& lv) {
+  Taps t;
+#pragma unroll
+  for (int k = 0; k <= kHalo; ++k) {
+    t.g[k] = lv.gauss[k];
+    asm("" : "+v"(t.g[k]));
+  }
+  return t;
+}
+
+// LDS writes of this wave before, LDS reads of this wave after.
+__device__ __forceinline__ void row_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+__global__ __launch_bounds__(kStripThreads, 4) void loss_strip_pass1(LossArgs a, LossViews lv) {
+  __shared__ float2 s_xy[3][kStaged + 6];
+  const int lane = threadIdx.x % kWave, ch = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const Strip w = loss_strip(lv, blockIdx.x, lane);
+  const Taps g = load_taps(lv);
+  float2* row = s_xy[ch];
+  const int y1 = min(w.y0 + kStripRows, w.height);  // end of the output rows
+  const bool out_col = w.x0 + lane < w.width;
+
+  // staged rows: the k-th is image row y0 - 5 + k
+  struct Loaded {
+    float x0, y0, x1, y1;
+  } ahead[kTaps];
+  auto load = [&](int k) {
+    const int py = min(max(w.y0 - kHalo + k, 0), w.height - 1);
+    const int64_t at = 3 * (w.pix_base + static_cast<int64_t>(py) * w.width) + ch;
+    const float *img = a.img + at, *tgt = a.target + at;
+    return Loaded{img[3 * w.c0], tgt[3 * w.c0], img[3 * w.c1], tgt[3 * w.c1]};
+  };
+#pragma unroll
+  for (int k = 0; k < kAhead; ++k) ahead[k] = load(k);
+
+  float hx[kTaps], hy[kTaps], hxx[kTaps], hyy[kTaps], hxy[kTaps], cx[kTaps], cy[kTaps];
+  double share = 0.0;
+  for (int k0 = 0; w.y0 + k0 - 2 * kHalo < y1; k0 += kTaps) {
+#pragma unroll
+    for (int k = 0; k < kTaps; ++k) {
+      const Loaded l = ahead[k];
+      ahead[(k + kAhead) % kTaps] = load(k0 + k + kAhead);
+      const int py = w.y0 - kHalo + k0 + k;
+      const bool in = py >= 0 && py < w.height;
+      row_fence();
+      row[lane] = w.in0 && in ? make_float2(l.x0, l.y0) : make_float2(0.f, 0.f);
+      if (lane < 2 * kHalo) row[kWave + lane] = w.in1 && in ? make_float2(l.x1, l.y1) : make_float2(0.f, 0.f);
+      row_fence();
+      float sx = 0.f, sy = 0.f, sxx = 0.f, syy = 0.f, sxy = 0.f;
+#pragma unroll
+      for (int b = 0; b < kTaps; ++b) {
+        const float2 xy = row[lane + b];
+        const float x = xy.x, y = xy.y;
+        sx = fmaf(g[b], x, sx);
+        sy = fmaf(g[b], y, sy);
+        sxx = fmaf(g[b], x * x, sxx);
+        syy = fmaf(g[b], y * y, syy);
+        sxy = fmaf(g[b], x * y, sxy);
+        if (b == kHalo) {
+          cx[k] = x;
+          cy[k] = y;
+        }
+      }
+      hx[k] = sx;
+      hy[k] = sy;
+      hxx[k] = sxx;
+      hyy[k] = syy;
+      hxy[k] = sxy;
+      const int oy = w.y0 + k0 + k - 2 * kHalo;  // the output row whose window ends here
+      if (oy < w.y0 || oy >= y1) continue;
+      // along the column, the oldest row first
+      float u = 0.f, v = 0.f;
+      sxx = syy = sxy = 0.f;
+#pragma unroll
+      for (int q = 0; q < kTaps; ++q) {
+        const int r = (k + 1 + q) % kTaps;
+        u = fmaf(g[q], hx[r], u);
+        v = fmaf(g[q], hy[r], v);
+        sxx = fmaf(g[q], hxx[r], sxx);
+        syy = fmaf(g[q], hyy[r], syy);
+        sxy = fmaf(g[q], hxy[r], sxy);
+      }
+      const float a1 = 2.f * u * v + kC1;
+      const float a2 = 2.f * (sxy - u * v) + kC2;
+      const float b1 = u * u + v * v + kC1;
+      const float b2 = (sxx - u * u) + (syy - v * v) + kC2;
+      const float ib = 1.f / (b1 * b2);
+      const float s = a1 * a2 * ib;
+      const float d_u = (2.f * v * a2 - 2.f * v * a1) * ib - s * (2.f * u / b1 - 2.f * u / b2);
+      const float d_sxx = -s / b2;
+      const float d_sxy = 2.f * a1 * ib;
+      if (out_col) {
+        const int64_t at = ch * a.total_pixels + w.pix_base + static_cast<int64_t>(oy) * w.width + w.x0;
+        (a.dmap2 + at)[lane] = make_float2(d_u, d_sxx);
+        (a.dmap1 + at)[lane] = d_sxy;
+        // this entry's part of L_v * V * P_v: (1 - lambda)|x - y| + lambda (1 - S)
+        const float x = cx[(k + 1 + kHalo) % kTaps], y = cy[(k + 1 + kHalo) % kTaps];
+        share += (1.0 - a.lambda) * fabs(static_cast<double>(x) - y) + a.lambda * (1.0 - static_cast<double>(s));
+      }
+    }
+  }
+#pragma unroll
+  for (int d = 32; d >= 1; d >>= 1) share += __shfl_xor(share, d, kWave);
+  if (lane == 0) a.part[static_cast<int64_t>(lv.tile0 + static_cast<int>(blockIdx.x)) * 3 + ch] = share * lv.scale[w.v];
+}
+
+// The gradient's rows go through LDS so that the three waves' channels are
+// stored interleaved, whole rows at a time.
+__global__ __launch_bounds__(kStripThreads, 4) void loss_strip_pass2(LossArgs a, LossViews lv) {
+  __shared__ float2 s_m2[3][kStaged + 6];
+  __shared__ float s_m1[3][kStaged + 6];
+  __shared__ float s_out[kTaps][3 * kStrip];
+  const int lane = threadIdx.x % kWave, ch = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const Strip w = loss_strip(lv, blockIdx.x, lane);
+  const Taps g = load_taps(lv);
+  float2* row2 = s_m2[ch];
+  float* row1 = s_m1[ch];
+  const int y1 = min(w.y0 + kStripRows, w.height);
+  const int64_t plane = ch * a.total_pixels + w.pix_base;
+  const int cols = min(kStrip, w.width - w.x0);
+  const int oc = min(lane, cols - 1);  // output column read
+  const float sc = lv.scale[w.v], lambda = a.lambda;
+
+  struct Loaded {
+    float2 m0, m1;
+    float n0, n1, x, y;  // (x, y): the output pixel whose window ends with this row
+  } ahead[kTaps];
+  auto load = [&](int k) {
+    const int py = min(max(w.y0 - kHalo + k, 0), w.height - 1);
+    const int64_t at = plane + static_cast<int64_t>(py) * w.width;
+    const float2* m2 = a.dmap2 + at;
+    const float* m1 = a.dmap1 + at;
+    const int oy = min(max(w.y0 + k - 2 * kHalo, 0), w.height - 1);
+    const int64_t o = 3 * (w.pix_base + static_cast<int64_t>(oy) * w.width + w.x0) + ch;
+    return Loaded{m2[w.c0], m2[w.c1], m1[w.c0], m1[w.c1], (a.img + o)[3 * oc], (a.target + o)[3 * oc]};
+  };
+#pragma unroll
+  for (int k = 0; k < kAhead; ++k) ahead[k] = load(k);
+
+  float h0[kTaps], h1[kTaps], h2[kTaps];
+  for (int k0 = 0; w.y0 + k0 - 2 * kHalo < y1; k0 += kTaps) {
+#pragma unroll
+    for (int k = 0; k < kTaps; ++k) {
+      const Loaded l = ahead[k];
+      ahead[(k + kAhead) % kTaps] = load(k0 + k + kAhead);
+      const int py = w.y0 - kHalo + k0 + k;
+      const bool in = py >= 0 && py < w.height;
+      row_fence();
+      row2[lane] = w.in0 && in ? l.m0 : make_float2(0.f, 0.f);
+      row1[lane] = w.in0 && in ? l.n0 : 0.f;
+      if (lane < 2 * kHalo) {
+        row2[kWave + lane] = w.in1 && in ? l.m1 : make_float2(0.f, 0.f);
+        row1[kWave + lane] = w.in1 && in ? l.n1 : 0.f;
+      }
+      row_fence();
+      float s0 = 0.f, s1 = 0.f, s2 = 0.f;
+#pragma unroll
+      for (int b = 0; b < kTaps; ++b) {
+        const float2 m = row2[lane + b];
+        s0 = fmaf(g[b], m.x, s0);
+        s1 = fmaf(g[b], m.y, s1);
+        s2 = fmaf(g[b], row1[lane + b], s2);
+      }
+      h0[k] = s0;
+      h1[k] = s1;
+      h2[k] = s2;
+      const int oy = w.y0 + k0 + k - 2 * kHalo;
+      if (oy < w.y0 || oy >= y1) continue;
+      float f0 = 0.f, f1 = 0.f, f2 = 0.f;
+#pragma unroll
+      for (int q = 0; q < kTaps; ++q) {
+        const int r = (k + 1 + q) % kTaps;
+        f0 = fmaf(g[q], h0[r], f0);
+        f1 = fmaf(g[q], h1[r], f1);
+        f2 = fmaf(g[q], h2[r], f2);
+      }
+      const float x = l.x, y = l.y;
+      const float sgn = x > y ? 1.f : (x < y ? -1.f : 0.f);
+      const float dmean = f0 + 2.f * x * f1 + y * f2;
+      s_out[k][3 * lane + ch] = sc * ((1.f - lambda) * sgn - lambda * dmean);
+    }
+    __syncthreads();
+    const int t = static_cast<int>(threadIdx.x);
+#pragma unroll
+    for (int k = 0; k < kTaps; ++k) {
+      const int oy = w.y0 + k0 + k - 2 * kHalo;
+      if (oy < w.y0 || oy >= y1 || t >= 3 * cols) continue;
+      (a.dL + 3 * (w.pix_base + static_cast<int64_t>(oy) * w.width + w.x0))[t] = s_out[k][t];
+    }
+    __syncthreads();
+  }
+}
+
+// Sum of the tiles' shares in a fixed order: one block, strided partial sums,
 // then a tree over the block.
 __global__ __launch_bounds__(256) void loss_finalize(const double* part, int64_t n, float* loss) {
   __shared__ double s_red[4];
@@ -286,84 +541,77 @@ void gauss_taps(float* g) {
 
 }  // namespace
 
-int64_t loss_tiles(const wsr_camera* cams, int32_t nv) {
+// Tiles of all views, `w` by `h` pixels each.
+int64_t loss_tiles(const wsr_camera* cams, int32_t nv, int w, int h) {
   int64_t t = 0;
   for (int v = 0; v < nv; ++v)
-    t += static_cast<int64_t>((cams[v].width + kLT - 1) / kLT) * ((cams[v].height + kLT - 1) / kLT);
+    t += static_cast<int64_t>((cams[v].width + w - 1) / w) * ((cams[v].height + h - 1) / h);
   return t;
+}
+
+// Strips from kStripPixels pixels on, where they are filled well (narrow views
+// would leave lanes idle, and have too little room for the shares, which the
+// workspace holds for 16 x 16 tiles).
+constexpr int64_t kStripPixels = 450000;
+bool use_strips(const wsr_camera* cams, int32_t nv, int64_t pixels) {
+  return pixels >= kStripPixels && 2 * kStrip * kStripRows * loss_tiles(cams, nv, kStrip, kStripRows) <= 3 * pixels;
 }
 
 int64_t loss_workspace_bytes(const wsr_camera* cams, int32_t nv) {
   int64_t pixels = 0;
   for (int v = 0; v < nv; ++v) pixels += static_cast<int64_t>(cams[v].width) * cams[v].height;
   const int64_t maps = (sizeof(float) * 9 * pixels + 255) / 256 * 256;
-  return maps + static_cast<int64_t>(sizeof(double)) * 3 * loss_tiles(cams, nv);
+  return maps + static_cast<int64_t>(sizeof(double)) * 3 * loss_tiles(cams, nv, kLT, kLT);
 }
 
 hipError_t launch_loss(const wsr_camera* cams, int32_t nv, const float* img, const float* target, float lambda,
                        void* ws, float* loss, float* dL, hipStream_t st) {
-  hipError_t e = hipSuccess;
   int64_t pixels = 0;
   for (int v = 0; v < nv; ++v) pixels += static_cast<int64_t>(cams[v].width) * cams[v].height;
   LossArgs a;
   a.img = img;
   a.target = target;
   a.dmaps = static_cast<float*>(ws);
+  a.dmap2 = static_cast<float2*>(ws);
+  a.dmap1 = static_cast<float*>(ws) + 6 * pixels;
   a.part = reinterpret_cast<double*>(static_cast<char*>(ws) + (sizeof(float) * 9 * pixels + 255) / 256 * 256);
   a.dL = dL;
   a.total_pixels = pixels;
   a.lambda = lambda;
-  int64_t pix_base = 0;
+  const bool strips = use_strips(cams, nv, pixels);
+  const int tw = strips ? kStrip : kLT, th = strips ? kStripRows : kLT;
   int32_t tile0 = 0;
-  for (int v0 = 0; v0 < nv; v0 += kLossViewsPerLaunch) {
-    LossViews lv = {};
-    gauss_taps(lv.gauss);
-    lv.nv = nv - v0 < kLossViewsPerLaunch ? nv - v0 : kLossViewsPerLaunch;
-    lv.tile0 = tile0;
-    int32_t tiles = 0;
-    for (int k = 0; k < lv.nv; ++k) {
-      const wsr_camera& c = cams[v0 + k];
-      lv.width[k] = c.width;
-      lv.height[k] = c.height;
-      lv.tiles_x[k] = (c.width + kLT - 1) / kLT;
-      lv.tile_base[k] = tiles;
-      lv.pix_base[k] = pix_base;
-      lv.scale[k] = static_cast<float>(1.0 / (3.0 * c.width * c.height * nv));
-      tiles += lv.tiles_x[k] * ((c.height + kLT - 1) / kLT);
-      pix_base += static_cast<int64_t>(c.width) * c.height;
+  for (int pass = 1; pass <= 2; ++pass) {
+    int64_t pix_base = 0;
+    tile0 = 0;
+    for (int v0 = 0; v0 < nv; v0 += kLossViewsPerLaunch) {
+      LossViews lv = {};
+      gauss_taps(lv.gauss);
+      lv.nv = nv - v0 < kLossViewsPerLaunch ? nv - v0 : kLossViewsPerLaunch;
+      lv.tile0 = tile0;
+      int32_t tiles = 0;
+      for (int k = 0; k < lv.nv; ++k) {
+        const wsr_camera& c = cams[v0 + k];
+        lv.width[k] = c.width;
+        lv.height[k] = c.height;
+        lv.tiles_x[k] = (c.width + tw - 1) / tw;
+        lv.tile_base[k] = tiles;
+        lv.pix_base[k] = pix_base;
+        lv.scale[k] = static_cast<float>(1.0 / (3.0 * c.width * c.height * nv));
+        tiles += lv.tiles_x[k] * ((c.height + th - 1) / th);
+        pix_base += static_cast<int64_t>(c.width) * c.height;
+      }
+      lv.tile_base[lv.nv] = tiles;
+      tile0 += tiles;
+      if (tiles == 0) continue;
+      const unsigned count = static_cast<unsigned>(tiles);
+      if (strips && pass == 1) loss_strip_pass1<<<count, kStripThreads, 0, st>>>(a, lv);
+      else if (strips) loss_strip_pass2<<<count, kStripThreads, 0, st>>>(a, lv);
+      else if (pass == 1) loss_pass1<<<dim3(count, 3), 256, 0, st>>>(a, lv);
+      else loss_pass2<<<dim3(count, 3), 256, 0, st>>>(a, lv);
+      const hipError_t e = hipGetLastError();
+      if (e != hipSuccess) return e;
     }
-    lv.tile_base[lv.nv] = tiles;
-    if (tiles > 0) {
-      loss_pass1<<<dim3(static_cast<unsigned>(tiles), 3), 256, 0, st>>>(a, lv);
-      if ((e = hipGetLastError()) != hipSuccess) return e;
-    }
-    tile0 += tiles;
-  }
-  pix_base = 0;
-  tile0 = 0;
-  for (int v0 = 0; v0 < nv; v0 += kLossViewsPerLaunch) {
-    LossViews lv = {};
-    gauss_taps(lv.gauss);
-    lv.nv = nv - v0 < kLossViewsPerLaunch ? nv - v0 : kLossViewsPerLaunch;
-    lv.tile0 = tile0;
-    int32_t tiles = 0;
-    for (int k = 0; k < lv.nv; ++k) {
-      const wsr_camera& c = cams[v0 + k];
-      lv.width[k] = c.width;
-      lv.height[k] = c.height;
-      lv.tiles_x[k] = (c.width + kLT - 1) / kLT;
-      lv.tile_base[k] = tiles;
-      lv.pix_base[k] = pix_base;
-      lv.scale[k] = static_cast<float>(1.0 / (3.0 * c.width * c.height * nv));
-      tiles += lv.tiles_x[k] * ((c.height + kLT - 1) / kLT);
-      pix_base += static_cast<int64_t>(c.width) * c.height;
-    }
-    lv.tile_base[lv.nv] = tiles;
-    if (tiles > 0) {
-      loss_pass2<<<dim3(static_cast<unsigned>(tiles), 3), 256, 0, st>>>(a, lv);
-      if ((e = hipGetLastError()) != hipSuccess) return e;
-    }
-    tile0 += tiles;
   }
   loss_finalize<<<1, 256, 0, st>>>(a.part, static_cast<int64_t>(tile0) * 3, loss);
   return hipGetLastError();
