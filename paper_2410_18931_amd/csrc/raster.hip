@@ -33,42 +33,23 @@ namespace {
 // Every wave owns an 8x8 pixel block of the tile (one pixel per lane): tile 8
 // is one wave, tile 16 four, tile 32 sixteen.  Up to 256 records are staged
 // per batch.
-//
-// A splat is culled against sub-blocks: the 8 wide, 4 high halves of the 8x8
-// blocks, which it must pay for 10 to 24 % fewer pixels than for whole blocks
-// (1.45 -> 1.31 evaluated pixels per pixel in its support at 1 M Gaussians /
-// 1080p, 1.71 -> 1.48 at 200 k / 720p, 3.0 -> 2.3 at 30 k / 400 x 300).
-// Quarters (4 x 4) would save as much again, but a row of four pixels shares
-// its row terms among too few.  Tile 32 keeps whole blocks: its 32 halves'
-// culling masks would not fit the pair buffer.
 template <int T>
 struct TileGeom {
   static constexpr int kSub = 8;                       // wave block edge
   static constexpr int kWaves = (T / 8) * (T / 8);
-  static constexpr int kHalves = T == 32 ? 1 : 2;      // sub-blocks of a wave block, one above the other
-  static constexpr int kRows = 8 / kHalves;            // rows of a sub-block
-  static constexpr int kSubs = kWaves * kHalves;       // sub-blocks of the tile: wave block b's are b kHalves ..
   static constexpr int kThreads = kWaves * kWave;
   static constexpr int kBatch = kThreads < 256 ? kThreads : 256;
-  static_assert(kBatch <= 256, "the sorted composite's lists hold 8-bit record indices");
-  // first pixel centre of a sub-block relative to the tile's centre (exact)
-  static __device__ __forceinline__ float sub_x(int s) {
-    return static_cast<float>((s / kHalves % (T / 8)) * 8 - T / 2) + 0.5f;
-  }
-  static __device__ __forceinline__ float sub_y(int s) {
-    return static_cast<float>((s / kHalves / (T / 8)) * 8 + (s % kHalves) * kRows - T / 2) + 0.5f;
-  }
+  static_assert(kBatch <= 256, "the backward's lists hold 8-bit record indices");
 };
 
 // A record as staged in LDS for one tile (48 bytes; stage_and_cull builds it
 // from the projected record):
 //   r0 = (mx, my, A, B2)   centre relative to the tile's centre; conic
 //                          (A, B2 = 2B, C) times log2(e) / 2
-//   r1 = (c0, c1, c2, amp) colour (times amp in the forward)
-//   r2 = (C, ext | cut, u, K)  support half-extents (two halves), or with
+//   r1 = (C, amp, c0, c1)  colour (times amp in the forward)
+//   r2 = (c2, ext | cut, u, 0)  support half-extents (two halves), or with
 //                          the early-out the record's own cutoff times
-//                          log2(e) / 2 and its support_k; u = the opacity,
-//                          used by OIT only
+//                          log2(e) / 2; u = the opacity, used by OIT only
 // The tile-relative centre is (integer origin - tile centre) + fractional
 // centre: the difference is exact, the sum rounds once (to within 2^-24 of
 // its magnitude, which is at most the pixel's distance plus half the tile
@@ -98,66 +79,11 @@ __device__ __forceinline__ float quad_form(float A, float B2dy, float Cdy2, floa
 __device__ __forceinline__ float pair_q(const StagedRec& r, float px, float py) {
   const float dx = px - r.r0.x;
   const float dy = py - r.r0.y;
-  return quad_form(r.r0.z, r.r0.w * dy, (r.r2.x * dy) * dy, dx);
+  return quad_form(r.r0.z, r.r0.w * dy, (r.r1.x * dy) * dy, dx);
 }
 
 // exp(-q/2) from the scaled form q log2(e) / 2
 __device__ __forceinline__ float falloff(float qs) { return __builtin_amdgcn_exp2f(-qs); }
-
-// Transcendentals of one row of eight pixels, back to back at raised wave
-// priority.  A SIMD issues two plain FP32 operations of different waves at
-// once (2.5 cycles per wave instruction with four or eight waves) but a
-// transcendental alone (8.5 cycles); scattered among the waves' other work
-// each one also breaks up pairs around it.  Issued as one burst that the other
-// waves let pass, they leave those to pair up again.  A loop of the forward's
-// operations per pixel took 44 cycles per wave with the exp2 in its natural
-// place or in bursts of eight, and 30.6 in bursts at raised priority; the
-// backward's 64.6 and 40.8.
-template <typename F>
-__device__ __forceinline__ void trans_burst(F&& f) {
-  __builtin_amdgcn_sched_barrier(0);
-  __builtin_amdgcn_s_setprio(3);
-  __builtin_amdgcn_sched_barrier(0);
-  f();
-  __builtin_amdgcn_sched_barrier(0);
-  __builtin_amdgcn_s_setprio(0);
-  __builtin_amdgcn_sched_barrier(0);
-}
-
-// The support predicate q <= cut as a factor in plain FP32 arithmetic, which
-// pairs with other waves' work (a compare and select are half-rate operations
-// with wait states between them): clamp(K - q 2^64) to [0, 1] with
-// K = 2^64 next(cut), next the following float.  K - q 2^64 is rounded once,
-// so it is <= 0 for q > cut (q >= next(cut)) and, an ulp of the cutoff being
-// at least 2^-64 for cut >= 2^-41, >= 1 for q <= cut.  A smaller cutoff
-// (tau = 0) keeps q = 0; one above 2^63 keeps every q, whose falloff is 0
-// there.  A NaN clamps to 0.  cut < 0 passes no pixel.
-constexpr float kSupportScale = 0x1p64f;
-__device__ __forceinline__ float support_k(float cut) {
-  return cut < 0.f ? -kSupportScale : fmaxf(__uint_as_float(__float_as_uint(cut) + 1u) * kSupportScale, 1.f);
-}
-__device__ __forceinline__ float in_support(float q, float K) {
-  return __builtin_amdgcn_fmed3f(fmaf(q, -kSupportScale, K), 0.f, 1.f);
-}
-
-// x m with 0 m = x 0 = 0 whatever the other factor, NaN included.
-__device__ __forceinline__ float mul_zero_wins(float x, float m) {
-  float r;
-  asm("v_mul_legacy_f32 %0, %1, %2" : "=v"(r) : "v"(x), "v"(m));
-  return r;
-}
-
-// exp(-q/2) of a row's eight pixels where q <= cut (K = support_k(cut)), else
-// 0, also where q is NaN.
-__device__ __forceinline__ void falloff_row(const float (&q)[8], float K, float (&G)[8]) {
-  float x[8];
-  trans_burst([&] {
-#pragma unroll
-    for (int k = 0; k < 8; ++k) x[k] = falloff(q[k]);
-  });
-#pragma unroll
-  for (int k = 0; k < 8; ++k) G[k] = mul_zero_wins(x[k], in_support(q[k], K));
-}
 
 __device__ __forceinline__ float2 rec_extent(const StagedRec& r) {
   const uint32_t e = __float_as_uint(r.r2.y);
@@ -166,85 +92,61 @@ __device__ __forceinline__ float2 rec_extent(const StagedRec& r) {
   return make_float2(static_cast<float>(ex), static_cast<float>(ey));
 }
 
-// Does the splat's support reach the pixel centres spanning
-// [bx, bx + 7] x [by, by + h] (relative to the tile's centre)?  First the
-// (conservative) support box; then, unless the conic is badly conditioned, the
-// exact minimum of q over the rectangle against tau with a margin far above
-// the float error of q.  The minimum is at the centre, or on one of the (at
-// most two) edges that face it: on the nearest vertical line at its clamped 1D
-// minimiser, or on the nearest horizontal one.  Where the centre lies within
-// the rectangle's columns the nearest vertical line passes through it and that
-// point is one of the rectangle, no further below the minimum.  For
-// needle-like splats (eigenvalue ratio above ~100) float q loses digits to
-// cancellation, so the box decision is kept.
+// Does the splat's support reach the wave block whose pixel centres span
+// [bx, bx + sub1] x [by, by + sub1] (relative to the tile's centre)?  First
+// the (conservative) support box; then, unless the conic is badly
+// conditioned, the exact minimum of q over
+// the block (the unconstrained minimum is the centre; otherwise the minimum
+// lies on an edge, at the clamped 1D minimiser of that edge) against tau with
+// a margin far above the float error of q.  For needle-like splats
+// (eigenvalue ratio above ~100) float q loses digits to cancellation, so the
+// box decision is kept.
 //
 // With CUT (the opacity early-out) the record's fourth word is the splat's
 // own cutoff instead of the half-extents, which are then derived from the
 // conic: the extents of q <= cut are sqrt(cut C / det) and sqrt(cut A / det),
 // with det = A C - B^2 formed by Kahan's algorithm (B^2 split exactly with an
 // FMA) so that it stays accurate for needle-like conics.
-struct SupportBox {
-  float ex, ey;     // half-extents with their rounding slack
-  float tau;        // cutoff with its margin (infinite where the box decides)
-  float kx, ky;     // -B / A, -B / C
-};
-
 template <bool CUT>
-__device__ __forceinline__ SupportBox support_box(const StagedRec& r, float tau_in) {
-  SupportBox b;
-  const float A = r.r0.z, B = 0.5f * r.r0.w, C = r.r2.x;
+__device__ __forceinline__ bool block_hits(const StagedRec& r, float bx, float by, float sub1, float tau_in) {
+  float2 e;
   float tau = tau_in;
   if (CUT) {
     tau = r.r2.y;
+    const float A = r.r0.z, B = 0.5f * r.r0.w, C = r.r1.x;
     const float bb = B * B;
     const float det = fmaf(A, C, -bb) - fmaf(B, B, -bb);
     const float s = det > 0.f ? tau * __builtin_amdgcn_rcpf(det) : __builtin_inff();
-    b.ex = sqrtf(s * C) * 1.0001f;
-    b.ey = sqrtf(s * A) * 1.0001f;
+    e = make_float2(sqrtf(s * C) * 1.0001f, sqrtf(s * A) * 1.0001f);
   } else {
-    const float2 e = rec_extent(r);
-    b.ex = e.x;
-    b.ey = e.y;
+    e = rec_extent(r);
   }
-  b.ex += 1e-3f * fabsf(r.r0.x) + 1e-2f;
-  b.ey += 1e-3f * fabsf(r.r0.y) + 1e-2f;
+  const float mx = r.r0.x, my = r.r0.y;
+  const float sx = 1e-3f * fabsf(mx) + 1e-2f, sy = 1e-3f * fabsf(my) + 1e-2f;  // rounding slack
+  if (!((mx + e.x + sx >= bx) && (mx - e.x - sx <= bx + sub1) && (my + e.y + sy >= by) &&
+        (my - e.y - sy <= by + sub1)))
+    return false;
+  const float A = r.r0.z, B = 0.5f * r.r0.w, C = r.r1.x;
   const float tr = A + C, det = A * C - B * B;
-  b.tau = tr * tr <= 102.f * det ? tau * 1.002f + 1e-3f : __builtin_inff();
+  if (!(tr * tr <= 102.f * det)) return true;
+  // block corners relative to the centre
+  const float x0 = bx - mx, x1 = (bx + sub1) - mx;
+  const float y0 = by - my, y1 = (by + sub1) - my;
+  if (x0 <= 0.f && x1 >= 0.f && y0 <= 0.f && y1 >= 0.f) return true;
   // hardware reciprocals (within 1 ulp): they only place the edge minimisers,
   // whose error changes q there by a second-order amount far inside the margin
-  b.kx = -B * __builtin_amdgcn_rcpf(A);
-  b.ky = -B * __builtin_amdgcn_rcpf(C);
-  return b;
-}
-
-// (without branches: the comparisons of the box are shared by the sub-blocks
-// of a column or row)
-__device__ __forceinline__ bool rect_hits(const StagedRec& r, const SupportBox& b, float bx, float by, float h) {
-  const float A = r.r0.z, B2 = r.r0.w, C = r.r2.x;
-  // the rectangle relative to the centre, and its nearest column and row
-  const float x0 = bx - r.r0.x, x1 = (bx + 7.f) - r.r0.x;
-  const float y0 = by - r.r0.y, y1 = (by + h) - r.r0.y;
-  const float cx = __builtin_amdgcn_fmed3f(0.f, x0, x1), cy = __builtin_amdgcn_fmed3f(0.f, y0, y1);
-  const float dy = __builtin_amdgcn_fmed3f(b.ky * cx, y0, y1);
-  const float qv = fmaf(fmaf(C, dy, B2 * cx), dy, (A * cx) * cx);
-  const float dx = __builtin_amdgcn_fmed3f(b.kx * cy, x0, x1);
-  const float qh = fmaf(fmaf(A, dx, B2 * cy), dx, (C * cy) * cy);
-  return static_cast<bool>(static_cast<int>(fabsf(cx) <= b.ex) & static_cast<int>(fabsf(cy) <= b.ey) &
-                           static_cast<int>(!(fminf(qv, qh) > b.tau)));
-}
-
-// The sub-blocks s0 .. s0 + N - 1 of the tile that the splat reaches, one bit
-// each (bit s0 + i).
-template <int T, int N, bool CUT>
-__device__ __forceinline__ uint32_t sub_hits(const StagedRec& r, float tau, bool valid, int s0) {
-  using G = TileGeom<T>;
-  SupportBox box = support_box<CUT>(r, tau);
-  if (!valid) box.ex = -1.f;
-  uint32_t h = 0;
+  const float iA = __builtin_amdgcn_rcpf(A), iC = __builtin_amdgcn_rcpf(C);
+  float qmin = 3.0e38f;
 #pragma unroll
-  for (int s = 0; s < N; ++s)
-    h |= rect_hits(r, box, G::sub_x(s0 + s), G::sub_y(s0 + s), G::kRows - 1) ? 1u << s : 0u;
-  return h << s0;
+  for (int k = 0; k < 2; ++k) {
+    const float dy = k ? y1 : y0;
+    const float dx = fminf(fmaxf(-B * dy * iA, x0), x1);
+    qmin = fminf(qmin, A * dx * dx + 2.f * B * dx * dy + C * dy * dy);
+    const float ex2 = k ? x1 : x0;
+    const float ey2 = fminf(fmaxf(-B * ex2 * iC, y0), y1);
+    qmin = fminf(qmin, A * ex2 * ex2 + 2.f * B * ex2 * ey2 + C * ey2 * ey2);
+  }
+  return qmin <= tau * 1.002f + 1e-3f;
 }
 
 struct RasterArgs {
@@ -287,10 +189,10 @@ struct RasterArgs {
   // persistent launches: the counter the workgroups take work items from
   // (zeroed before the launch); null for one workgroup per work item
   uint32_t* queue;
-  // culling masks: per list entry the sub-blocks of the tile its splat reaches
-  // (one bit each, HitBits<T> per entry), or null for none;
-  // flags->cull_masks says whether they hold the current lists' masks
-  void* masks;
+  // culling masks (see cull_mask_word), or null where the pair buffer has no
+  // room for them; flags->cull_masks says whether they hold the current
+  // lists' masks
+  uint64_t* masks;
   DevFlags* flags;
 };
 
@@ -326,10 +228,18 @@ struct TileCtx {
   int fx0, fy0;                   // frame origin of the staged centres: the tile's centre
 };
 
-// The sub-blocks of a tile, one bit each.
+// The culling masks: wave w's 64-bit ballot for the 64-entry group g of tile
+// t's list (entries list0 + 64 g ...) is word (list0 / 64 + t + g) W + w, W the
+// waves of a tile.  A tile of l entries has ceil(l / 64) groups and the next
+// tile's first group is at least floor((list0 + l) / 64) + t + 1, so the
+// tiles' words never overlap; all of them lie below
+// (ceil(capacity / 64) + tiles + 2) W.
 template <int T>
-using HitBits = typename std::conditional<(TileGeom<T>::kSubs <= 8), uint8_t, uint16_t>::type;
-static_assert(TileGeom<32>::kSubs <= 16, "sub-block bits");
+__device__ __forceinline__ int64_t cull_mask_word(const TileCtx<T>& c, uint32_t pos) {
+  constexpr int W = TileGeom<T>::kWaves;
+  const int64_t g = static_cast<int64_t>(c.list0 >> 6) + c.tile + ((pos - c.list0) >> 6);
+  return g * W + c.wave;
+}
 
 template <int T>
 __device__ __forceinline__ void tile_setup(const RasterArgs& a, uint32_t item, TileCtx<T>& c, const DevCamera*& cam) {
@@ -373,7 +283,7 @@ __device__ __forceinline__ void tile_setup(const RasterArgs& a, uint32_t item, T
   const uint64_t ee = ss + kItemSplats;
   c.start = static_cast<uint32_t>(ss < e0 ? ss : e0);
   c.end = static_cast<uint32_t>(ee < e0 ? ee : e0);
-  c.wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  c.wave = threadIdx.x / kWave;
   c.lane = threadIdx.x % kWave;
   c.bx0 = c.tx * T + (c.wave % (T / 8)) * G::kSub;
   c.by0 = c.ty * T + (c.wave / (T / 8)) * G::kSub;
@@ -383,70 +293,79 @@ __device__ __forceinline__ void tile_setup(const RasterArgs& a, uint32_t item, T
   c.py = c.by0 + (c.lane >> 3);
 }
 
-// The staged form of a projected record, relative to the tile centre
-// (tox, toy).
-template <bool CUT, bool OIT, bool PREMUL>
-__device__ __forceinline__ StagedRec make_staged(const DevSplat* d, float tox, float toy) {
-  const SplatRec s = d->s;  // (fx, fy, A, B2) (C, ox, oy, amp) (c0, c1, c2, ext | cut)
-  const float amp = s.r1.w;
-  float c0 = s.r2.x, c1 = s.r2.y, c2 = s.r2.z;
-  if (PREMUL) {
-    c0 *= amp;
-    c1 *= amp;
-    c2 *= amp;
-  }
-  StagedRec r;
-  r.r0 = make_float4((s.r1.y - tox) + s.r0.x, (s.r1.z - toy) + s.r0.y, s.r0.z * kHalfLog2e, s.r0.w * kHalfLog2e);
-  r.r1 = make_float4(c0, c1, c2, amp);
-  // OIT: the opacity u rides in the record's third word
-  r.r2 = make_float4(s.r1.x * kHalfLog2e, CUT ? s.r2.w * kHalfLog2e : s.r2.w, OIT ? __uint_as_float(d->slot.w) : 0.f,
-                     CUT ? support_k(s.r2.w * kHalfLog2e) : 0.f);
-  return r;
-}
-
-// Barrier between LDS writes and reads of a workgroup.  __syncthreads would
-// also wait for the outstanding global stores and loads.
-__device__ __forceinline__ void lds_barrier() {
-  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-}
-
-// LDS writes of this wave before, LDS reads of this wave after.
-__device__ __forceinline__ void lds_wave_fence() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-// For the sorted composite: stage one batch of records into LDS and list, in
-// order, those whose support reaches this wave's block (as staged-record
-// indices).  Returns the list length.
-template <int T, int BATCH>
+// Stage one batch of records into LDS (as StagedRec) and build this wave's
+// culled list.  Returns the list length.  With PREMUL (the forward) the
+// staged colour is premultiplied by the amplitude, so a pair adds G (amp c)
+// and G amp.  The list holds staged-record indices (uint8_t) or, as uint32_t,
+// their byte offsets in s_rec, which the forward uses as LDS addresses
+// directly.  With SLOTS (the backward), also the Gaussian-major slot of
+// each staged (tile, splat) pair -- the Gaussian's first slot plus this
+// tile's row-major index in its tile rectangle, the order in which binning
+// enumerated its pairs -- and, per staged record, its position in this
+// wave's list (0xffff if culled).
+template <int T, int BATCH, bool SLOTS, bool CUT, bool OIT, bool PREMUL, typename LT>
 __device__ __forceinline__ int stage_and_cull(const RasterArgs& a, const TileCtx<T>& c, uint32_t b,
-                                              StagedRec* s_rec, uint8_t* s_list) {
+                                              StagedRec* s_rec, uint32_t* s_slot, LT* s_list,
+                                              uint16_t* s_pos, uint64_t* mask_out = nullptr,
+                                              const uint64_t* mask_in = nullptr) {
   using G = TileGeom<T>;
   const float tox = static_cast<float>(c.fx0), toy = static_cast<float>(c.fy0);
   __syncthreads();  // previous batch fully consumed
   for (int q = threadIdx.x; q < BATCH; q += G::kThreads) {
     const uint32_t j = b + q;
-    if (j < c.end) s_rec[q] = make_staged<false, false, false>(a.rec + static_cast<int64_t>(c.v) * c.n + a.ent[j].x, tox, toy);
+    if (j < c.end) {
+      const uint2 en = a.ent[j];  // (Gaussian id, the pair's Gaussian-major slot)
+      const DevSplat* d = a.rec + static_cast<int64_t>(c.v) * c.n + en.x;
+      const SplatRec s = d->s;  // (fx, fy, A, B2) (C, ox, oy, amp) (c0, c1, c2, ext | cut)
+      const float amp = s.r1.w;
+      float c0 = s.r2.x, c1 = s.r2.y, c2 = s.r2.z;
+      if (PREMUL) {
+        c0 *= amp;
+        c1 *= amp;
+        c2 *= amp;
+      }
+      StagedRec r;
+      r.r0 = make_float4((s.r1.y - tox) + s.r0.x, (s.r1.z - toy) + s.r0.y, s.r0.z * kHalfLog2e,
+                         s.r0.w * kHalfLog2e);
+      r.r1 = make_float4(s.r1.x * kHalfLog2e, amp, c0, c1);
+      // OIT: the opacity u rides in the record's third word
+      r.r2 = make_float4(c2, CUT ? s.r2.w * kHalfLog2e : s.r2.w, OIT ? __uint_as_float(d->slot.w) : 0.f, 0.f);
+      s_rec[q] = r;
+      if (SLOTS) s_slot[q] = en.y;
+    }
   }
   __syncthreads();
   const int cnt = static_cast<int>(min(static_cast<uint32_t>(BATCH), c.end - b));
-  uint8_t* list = s_list + c.wave * BATCH;
+  LT* list = s_list + c.wave * BATCH;
   int m = 0;
   const float bx = static_cast<float>(c.bx0 - c.fx0) + 0.5f, by = static_cast<float>(c.by0 - c.fy0) + 0.5f;
   for (int k0 = 0; k0 < cnt; k0 += kWave) {
     const int k = k0 + c.lane;
-    bool hit = false;
-    if (k < cnt) {
-      const StagedRec& r = s_rec[k];
-      hit = rect_hits(r, support_box<false>(r, a.tau), bx, by, 7.f);
+    bool hit;
+    uint64_t mask;
+    if (mask_in) {
+      // the forward's ballot for these entries: the same test of the same
+      // staged values (the staged colour aside), so the same lists
+      mask = mask_in[cull_mask_word(c, b + k0)];
+      hit = ((mask >> c.lane) & 1ull) != 0;
+    } else {
+      hit = k < cnt && block_hits<CUT>(s_rec[k], bx, by, static_cast<float>(G::kSub - 1), a.tau);
+      mask = __ballot(hit);
+      if (mask_out && c.lane == 0) mask_out[cull_mask_word(c, b + k0)] = mask;
     }
-    const uint64_t mask = __ballot(hit);
-    if (hit) list[m + __popcll(mask & ((1ull << c.lane) - 1ull))] = static_cast<uint8_t>(k);
+    const int pos = m + __popcll(mask & ((1ull << c.lane) - 1ull));
+    if (hit) {
+      if constexpr (sizeof(LT) == 8)
+        list[pos] = LT{static_cast<uint32_t>(k * static_cast<int>(sizeof(StagedRec))), __float_as_uint(s_rec[k].r2.x)};
+      else
+        list[pos] = static_cast<LT>(sizeof(LT) == 1 ? k : k * static_cast<int>(sizeof(StagedRec)));
+    }
+    if (SLOTS && k < BATCH) s_pos[c.wave * BATCH + k] = hit ? static_cast<uint16_t>(pos) : 0xffffu;
     m += __popcll(mask);
   }
-  lds_wave_fence();
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   return m;
 }
 
@@ -490,272 +409,142 @@ __device__ __forceinline__ void write_pixel_oit(const RasterArgs& a, int64_t pix
   a.oit[pix] = make_float4(ar, ag, ab, P);
 }
 
-// The lanes of a forward wave: lane = (slot, row).  Row r of the 8x8 block is
-// evaluated by the eight lanes that hold it, each against another splat of the
-// row's sub-block list (slot s takes positions s, s + 8, ... of the lists of
-// the item's batches taken together), eight pixels per lane.  Against one
-// pixel per lane and one splat per step this shares a row's dy, B2 dy and
-// C dy^2 among eight pixels (9.5 instead of 14.25 VALU operations per pixel
-// and splat besides the exp2), one LDS read fetches eight records instead of
-// one (5 instead of 40 B of LDS per lane and splat), and the two halves of the
-// block walk lists of their own.
-constexpr int kFwdSlots = 8;
-
-// Sum over the slots (lane bits 3 to 5) of each row's eight columns, or their
-// product: three exchange steps, each halving the columns a lane still holds,
-// so that lane (slot, row) ends with column `slot` in v[0].
-template <bool PRODUCT, typename V>
-__device__ __forceinline__ V slots_combine(V (&v)[8], int lane) {
-#pragma unroll
-  for (int h = 4; h >= 1; h >>= 1) {
-    const bool hi = (lane & (8 * h)) != 0;
-#pragma unroll
-    for (int i = 0; i < h; ++i) {
-      const V lo_v = v[i], hi_v = v[i + h];
-      const V keep = hi ? hi_v : lo_v, send = hi ? lo_v : hi_v;
-      const V got = __shfl_xor(send, 8 * h, kWave);
-      v[i] = PRODUCT ? keep * got : keep + got;
-    }
-  }
-  return v[0];
+__device__ __forceinline__ const StagedRec& rec_at(const StagedRec* base, uint32_t off) {
+  return *reinterpret_cast<const StagedRec*>(reinterpret_cast<const char*>(base) + off);
 }
 
-// LDS of the forward.  Lists hold byte offsets into `rec`, which serve as LDS
-// addresses directly; they are cleared once, so that an entry past the end of
-// a list, read ahead but not used, is a valid offset too.  Behind the batch's
-// records, `rec` holds up to eight records per sub-block carried over from the
-// batch before: those of its last, incomplete group of eight.
-template <int T, int S>
-struct FwdShared {
-  using G = TileGeom<T>;
-  static constexpr int kGroups = S / kWave;              // groups of 64 records per batch
-  static constexpr int kParts = G::kWaves / kGroups;     // waves that share a group's culling
-  static constexpr int kList = S + 3 * kFwdSlots;        // entries of a list: carried, new, read ahead
-  StagedRec rec[S + G::kSubs * kFwdSlots];
-  uint16_t list[G::kSubs * kList];
-  HitBits<T> hits[kParts][S];
+// The first two vectors of a staged record (centre, conic, amplitude and two
+// premultiplied colours): with 8-byte list entries, whose second word holds
+// the third colour, a forward step reads two 16-byte vectors per record.
+struct StagedHead {
+  float4 r0, r1;
 };
+__device__ __forceinline__ StagedHead head_at(const StagedRec* base, uint32_t off) {
+  const StagedRec& r = rec_at(base, off);
+  return StagedHead{r.r0, r.r1};
+}
+
+// List entry type of the forward: with the weighted sum of Eq. 7 (no
+// per-splat cutoff, no opacity), (record byte offset, third premultiplied
+// colour), so that one 16-byte read fetches two entries and a step reads
+// 2.5 LDS vectors instead of 3.25; otherwise the byte offset alone.
+template <bool CUT, bool OIT>
+using FwdList = typename std::conditional<!CUT && !OIT, uint2, uint32_t>::type;
 
 // The forward of one work item (tile_setup's c), S records staged per batch.
-// Thread k stages record k, requested while the previous batch is evaluated;
-// each wave tests one group of 64 records against a share of the tile's
-// sub-blocks, and the waves then list the records that reach their own.  A
-// sub-block's groups of eight splats run on across the batches, so the order
-// of every pixel's sums follows from the list alone, whatever the batch size.
 template <int T, int S, bool COUNT, bool CUT, bool OIT>
 __device__ __forceinline__ void raster_fwd_item(const RasterArgs& a, const TileCtx<T>& c, const DevCamera* cam,
-                                                FwdShared<T, S>& sh) {
-  using G = TileGeom<T>;
-  using F = FwdShared<T, S>;
-  constexpr int NT = G::kSubs / F::kParts;  // sub-blocks each wave tests
-  constexpr bool kOwn = F::kParts == 1;     // a wave tests the records its threads stage
-  static_assert(S <= G::kThreads && G::kWaves % F::kGroups == 0 && G::kSubs % F::kParts == 0, "culling shares");
-  float nr[8], ng[8], nb[8], dd[8];
-  float cov[8];  // OIT: prod (1 - alpha)
-  int cntp[8];
-#pragma unroll
-  for (int k = 0; k < 8; ++k) {
-    nr[k] = ng[k] = nb[k] = dd[k] = 0.f;
-    cov[k] = 1.f;
-    cntp[k] = 0;
-  }
-  const int slot = c.lane >> 3, row = c.lane & 7;
-  const int half = row / G::kRows;
-  // pixel centres relative to the tile's centre (exact): the row's y and the
-  // block's columns
-  const float pcy = static_cast<float>(c.by0 + row - c.fy0) + 0.5f;
-  float xs[8];  // wave-uniform: kept in scalar registers
-#pragma unroll
-  for (int k = 0; k < 8; ++k)
-    xs[k] = __uint_as_float(
-        __builtin_amdgcn_readfirstlane(__float_as_uint(static_cast<float>(c.bx0 + k - c.fx0) + 0.5f)));
-  const float none = support_k(-1.f), Kall = support_k(a.tau);
-
-  const float tox = static_cast<float>(c.fx0), toy = static_cast<float>(c.fy0);
-  const DevSplat* recs = a.rec + static_cast<int64_t>(c.v) * c.n;
-  StagedRec mine = {};  // the record this thread stages next
-  auto fetch = [&](uint32_t b) {
-    const uint32_t j = b + threadIdx.x;
-    if (threadIdx.x < S && j < c.end) mine = make_staged<CUT, OIT, true>(recs + a.ent[j].x, tox, toy);
-  };
-  fetch(c.start);
-
-  // this lane's record of the present group: the geometry is replaced by the
-  // next group's as soon as q is formed, the rest after the sums
-  float4 r0, r1;
-  float C, u = 0.f, Kown = 0.f;
-  auto at_offset = [&](uint32_t off) -> const StagedRec& {
-    return *reinterpret_cast<const StagedRec*>(reinterpret_cast<const char*>(sh.rec) + off);
-  };
-  auto load_geom = [&](uint32_t off) {
-    r0 = at_offset(off).r0;
-    C = at_offset(off).r2.x;
-  };
-  auto load_rest = [&](uint32_t off) {
-    r1 = at_offset(off).r1;
-    if (OIT) u = at_offset(off).r2.z;
-    if (CUT) Kown = at_offset(off).r2.w;
-  };
-  // q of the row's pixels, then next_geom, then the sums; the staged colour
-  // carries the amplitude
-  auto evaluate = [&](bool use, auto&& next_geom) {
-    const float K = use ? (CUT ? Kown : Kall) : none;
-    const float dy = pcy - r0.y;
-    const float B2dy = r0.w * dy, Cdy2 = (C * dy) * dy;
-    float q[8], g[8];
-#pragma unroll
-    for (int k = 0; k < 8; ++k) q[k] = quad_form(r0.z, B2dy, Cdy2, xs[k] - r0.x);
-    next_geom();
-    falloff_row(q, K, g);
-#pragma unroll
-    for (int k = 0; k < 8; ++k) {
-      nr[k] = fmaf(g[k], r1.x, nr[k]);
-      ng[k] = fmaf(g[k], r1.y, ng[k]);
-      nb[k] = fmaf(g[k], r1.z, nb[k]);
-      dd[k] = fmaf(g[k], r1.w, dd[k]);
-      if (OIT) cov[k] *= 1.f - __builtin_amdgcn_fmed3f(u * g[k], 0.f, 1.f);
-      if (COUNT) cntp[k] += static_cast<int>(in_support(q[k], K));
-    }
-  };
-  // this wave's lists (of its sub-blocks), and this lane's
-  uint16_t* const lists = sh.list + c.wave * G::kHalves * F::kList;
-  const uint16_t* const list = lists + half * F::kList;
-  // this lane's slot among its sub-block's carried records
-  const int mysub = c.wave * G::kHalves + half;
-  const uint32_t carry = static_cast<uint32_t>((S + mysub * kFwdSlots + slot) * sizeof(StagedRec));
-  int held[G::kHalves] = {};  // carried records of each sub-block
+                                                StagedRec* s_rec, FwdList<CUT, OIT>* s_list) {
+  using LT = FwdList<CUT, OIT>;
+  float nr = 0.f, ng = 0.f, nb = 0.f, dd = 0.f;
+  float cov = 1.f;  // OIT: prod (1 - alpha)
+  int cntp = 0;
+  // this lane's pixel centre relative to the tile's centre (exact)
+  const float pcx = static_cast<float>(c.px - c.fx0) + 0.5f;
+  const float pcy = static_cast<float>(c.py - c.fy0) + 0.5f;
+  const float tau = a.tau;
   for (uint32_t b = c.start; b < c.end; b += S) {
-    const int cnt = static_cast<int>(min(static_cast<uint32_t>(S), c.end - b));
-    const int groups = (cnt + kWave - 1) / kWave;
-    lds_barrier();  // previous batch fully consumed
-    if (threadIdx.x < S) sh.rec[threadIdx.x] = mine;
-    if (!kOwn) lds_barrier();
-    {
-      const int g = kOwn ? c.wave : c.wave % F::kGroups, part = kOwn ? 0 : c.wave / F::kGroups;
-      const int k = g * kWave + c.lane;
-      if (g < groups)
-        sh.hits[part][k] =
-            static_cast<HitBits<T>>(sub_hits<T, NT, CUT>(kOwn ? mine : sh.rec[k], a.tau, k < cnt, part * NT));
-    }
-    lds_barrier();
-    if (a.masks && threadIdx.x < cnt) {
-      uint32_t h = 0;
-#pragma unroll
-      for (int part = 0; part < F::kParts; ++part) h |= sh.hits[part][threadIdx.x];
-      static_cast<HitBits<T>*>(a.masks)[b + threadIdx.x] = static_cast<HitBits<T>>(h);
-    }
-    fetch(b + S);
-    int n[G::kHalves];  // records of each sub-block: carried and new
-#pragma unroll
-    for (int h = 0; h < G::kHalves; ++h) {
-      n[h] = held[h];
-      if (half == h && slot < held[h]) lists[h * F::kList + slot] = static_cast<uint16_t>(carry);
-    }
-#pragma unroll
-    for (int g = 0; g < F::kGroups; ++g) {
-      if (g >= groups) break;
-      const uint32_t bits = sh.hits[c.wave * G::kHalves / NT][g * kWave + c.lane];
-#pragma unroll
-      for (int h = 0; h < G::kHalves; ++h) {
-        const bool hit = (bits >> (c.wave * G::kHalves + h)) & 1u;
-        const uint64_t w = __ballot(hit);
-        if (hit)
-          lists[h * F::kList + n[h] + __popcll(w & ((1ull << c.lane) - 1ull))] =
-              static_cast<uint16_t>((g * kWave + c.lane) * sizeof(StagedRec));
-        n[h] += __popcll(w);
+    const int m = stage_and_cull<T, S, false, CUT, OIT, true, LT>(a, c, b, s_rec, nullptr, s_list, nullptr,
+                                                                  a.masks);
+    const LT* list = s_list + c.wave * S;
+    // four splats per step: one read fetches their list entries and all four
+    // records are requested before any arithmetic, so LDS latency is paid
+    // once per four splats.  The staged colour carries the amplitude.
+    auto accumulate = [&](const StagedRec& r) {
+      const float q = pair_q(r, pcx, pcy);
+      const float cut = CUT ? r.r2.y : tau;
+      const float G = q <= cut ? falloff(q) : 0.f;
+      nr = fmaf(G, r.r1.z, nr);
+      ng = fmaf(G, r.r1.w, ng);
+      nb = fmaf(G, r.r2.x, nb);
+      dd = fmaf(G, r.r1.y, dd);
+      if (OIT) cov *= 1.f - __builtin_amdgcn_fmed3f(r.r2.z * G, 0.f, 1.f);
+      if (COUNT) cntp += q <= cut ? 1 : 0;
+    };
+    int i = 0;
+    if constexpr (sizeof(LT) == 8) {
+      // the same arithmetic as accumulate, with the third colour from the entry
+      auto accumulate_head = [&](const StagedHead& r, float cb) {
+        const float dx = pcx - r.r0.x;
+        const float dy = pcy - r.r0.y;
+        const float q = quad_form(r.r0.z, r.r0.w * dy, (r.r1.x * dy) * dy, dx);
+        const float G = q <= tau ? falloff(q) : 0.f;
+        nr = fmaf(G, r.r1.z, nr);
+        ng = fmaf(G, r.r1.w, ng);
+        nb = fmaf(G, cb, nb);
+        dd = fmaf(G, r.r1.y, dd);
+        if (COUNT) cntp += q <= tau ? 1 : 0;
+      };
+      for (; i + 4 <= m; i += 4) {
+        const uint4 e01 = *reinterpret_cast<const uint4*>(list + i);
+        const uint4 e23 = *reinterpret_cast<const uint4*>(list + i + 2);
+        const StagedHead r0 = head_at(s_rec, e01.x);
+        const StagedHead r1 = head_at(s_rec, e01.z);
+        const StagedHead r2 = head_at(s_rec, e23.x);
+        const StagedHead r3 = head_at(s_rec, e23.z);
+        accumulate_head(r0, __uint_as_float(e01.y));
+        accumulate_head(r1, __uint_as_float(e01.w));
+        accumulate_head(r2, __uint_as_float(e23.y));
+        accumulate_head(r3, __uint_as_float(e23.w));
       }
-    }
-    lds_wave_fence();
-    int rounds = 0, mine_rounds = 0;  // groups of eight: the longer half's, this lane's
-#pragma unroll
-    for (int h = 0; h < G::kHalves; ++h) {
-      rounds = max(rounds, n[h] / kFwdSlots);
-      if (half == h) mine_rounds = n[h] / kFwdSlots;
-    }
-    const uint16_t* next = list + slot;
-    uint32_t off = next[0];
-    load_geom(off);
-    load_rest(off);
-    off = next[kFwdSlots];
-    next += 2 * kFwdSlots;
-    for (int i = 0; i < rounds; ++i) {
-      evaluate(i < mine_rounds, [&] { load_geom(off); });
-      load_rest(off);
-      off = *next;
-      next += kFwdSlots;
-    }
-    // the incomplete groups' records are carried over: row j of a sub-block's
-    // first three copies the j-th third of its slot's record
-#pragma unroll
-    for (int h = 0; h < G::kHalves; ++h) {
-      held[h] = n[h] % kFwdSlots;
-      const int j = row % G::kRows;
-      if (half == h && slot < held[h] && j < 3) {
-        const uint32_t src = list[n[h] - held[h] + slot];
-        const float4 x = reinterpret_cast<const float4*>(&at_offset(src))[j];
-        reinterpret_cast<float4*>(const_cast<StagedRec*>(&at_offset(carry)))[j] = x;
+      for (; i < m; ++i) {
+        const uint2 e = list[i];
+        accumulate_head(head_at(s_rec, e.x), __uint_as_float(e.y));
       }
-    }
-    lds_wave_fence();
-  }
-  {
-    bool use = false, any = false;
-#pragma unroll
-    for (int h = 0; h < G::kHalves; ++h) {
-      any |= held[h] > 0;
-      if (half == h) use = slot < held[h];
-    }
-    if (any) {
-      load_geom(carry);
-      load_rest(carry);
-      evaluate(use, [] {});
+    } else {
+      for (; i + 4 <= m; i += 4) {
+        const uint4 o4 = *reinterpret_cast<const uint4*>(list + i);
+        const StagedRec r0 = rec_at(s_rec, o4.x);
+        const StagedRec r1 = rec_at(s_rec, o4.y);
+        const StagedRec r2 = rec_at(s_rec, o4.z);
+        const StagedRec r3 = rec_at(s_rec, o4.w);
+        accumulate(r0);
+        accumulate(r1);
+        accumulate(r2);
+        accumulate(r3);
+      }
+      for (; i < m; ++i) accumulate(rec_at(s_rec, list[i]));
     }
   }
-
-  const float Nr = slots_combine<false>(nr, c.lane), Ng = slots_combine<false>(ng, c.lane);
-  const float Nb = slots_combine<false>(nb, c.lane), Dd = slots_combine<false>(dd, c.lane);
-  const float Cv = OIT ? slots_combine<true>(cov, c.lane) : 1.f;
-  const int count = COUNT ? slots_combine<false>(cntp, c.lane) : 0;
-  const int px = c.bx0 + slot, py = c.by0 + row;  // the pixel this lane ends with
-  if (px >= cam->width || py >= cam->height) return;
-  const int64_t pix = cam->pix_base + static_cast<int64_t>(py) * cam->width + px;
-  if (COUNT) atomicAdd(a.out_count + pix, count);
+  if (c.px >= cam->width || c.py >= cam->height) return;
+  const int64_t pix = cam->pix_base + static_cast<int64_t>(c.py) * cam->width + c.px;
+  if (COUNT) atomicAdd(a.out_count + pix, cntp);
   if (c.nk > 1) {
     // split tile: this item's partial sums, added in item order by
     // raster_fwd_finalize (the coverage products of the parts multiply, so
     // their logarithms add).  Item 0 stores into the per-pixel accumulator,
     // item k > 0 into its own slot of the split-tile partials.
-    const float4 sums = make_float4(Nr, Ng, Nb, Dd);
+    const float4 sums = make_float4(nr, ng, nb, dd);
     if (c.k == 0) {
       reinterpret_cast<float4*>(a.acc)[pix] = sums;
-      if (OIT) a.acclog[pix] = __logf(Cv);
+      if (OIT) a.acclog[pix] = __logf(cov);
     } else {
       const int64_t e = static_cast<int64_t>(a.items[c.tile]) - c.tile + c.k - 1;
       if (e < a.split_slots) {
-        const int64_t q = e * (T * T) + (py - c.ty * T) * T + (px - c.tx * T);
+        const int64_t q = e * (T * T) + (c.py - c.ty * T) * T + (c.px - c.tx * T);
         a.split4[q] = sums;
-        if (OIT) a.splitlog[q] = __logf(Cv);
+        if (OIT) a.splitlog[q] = __logf(cov);
       }
     }
     return;
   }
   if (OIT)
-    write_pixel_oit(a, pix, Nr, Ng, Nb, Dd, Cv);
+    write_pixel_oit(a, pix, nr, ng, nb, dd, cov);
   else
-    write_pixel(a, pix, Nr, Ng, Nb, Dd);
+    write_pixel(a, pix, nr, ng, nb, dd);
 }
 
 // Forward.  Lists hold LDS byte offsets of the staged records.  S records
 // are staged per batch.  A workgroup renders the work item of dispatch slot
 // blockIdx.x (the grid covers them all), or, PERSIST, claims slots from a
-// counter until none is left.  Tile 16 asks for four waves per SIMD (at most
-// 128 VGPRs): five spill, 412 instead of 386 us at 1 M Gaussians / 1080p.
+// counter until none is left.
 template <int T, int S, bool COUNT, bool CUT, bool OIT, bool PERSIST>
-__global__ __launch_bounds__(TileGeom<T>::kThreads, T == 16 ? 4 : 1) void raster_fwd_kernel(RasterArgs a) {
-  __shared__ FwdShared<T, S> sh;
+__global__ __launch_bounds__(TileGeom<T>::kThreads) void raster_fwd_kernel(RasterArgs a) {
+  using G = TileGeom<T>;
+  using LT = FwdList<CUT, OIT>;
+  __shared__ StagedRec s_rec[S];
+  __shared__ __align__(16) LT s_list[G::kWaves * S];
   __shared__ uint32_t s_item;
-  for (int k = threadIdx.x; k < TileGeom<T>::kSubs * FwdShared<T, S>::kList; k += TileGeom<T>::kThreads) sh.list[k] = 0;
-  for (int k = threadIdx.x; k < TileGeom<T>::kSubs * kFwdSlots; k += TileGeom<T>::kThreads) sh.rec[S + k] = StagedRec{};
   // every work item stores its waves' culling masks (when there is room):
   // valid for the backward once this launch has finished
   if (blockIdx.x == 0 && threadIdx.x == 0) a.flags->cull_masks = a.masks ? (kCullMasks | (CUT ? 2u : 0u)) : 0u;
@@ -765,7 +554,7 @@ __global__ __launch_bounds__(TileGeom<T>::kThreads, T == 16 ? 4 : 1) void raster
     TileCtx<T> c;
     const DevCamera* cam;
     tile_setup<T>(a, item, c, cam);
-    raster_fwd_item<T, S, COUNT, CUT, OIT>(a, c, cam, sh);
+    raster_fwd_item<T, S, COUNT, CUT, OIT>(a, c, cam, s_rec, s_list);
     if (!PERSIST) break;
     item = claim_item(a, &s_item);
   }
@@ -809,25 +598,20 @@ __global__ __launch_bounds__(256) void raster_fwd_finalize(RasterArgs a) {
   }
 }
 
-// Per-pixel factors of a sub-block in LDS: its pixels', and one of padding, so
-// that the same pixel of different sub-blocks lies in different banks.
-template <int T>
-constexpr int kPdStride = TileGeom<T>::kRows * 8 + 1;
-
 __device__ __forceinline__ float wave_sum(float x) {
 #pragma unroll
   for (int d = 32; d >= 1; d >>= 1) x += __shfl_xor(x, d, kWave);
   return x;
 }
 
-// Moments of a block.  A lane sums, per pixel of its splat's walk,
-// e = G dL/da against the pixel centre's offset xc from the 8x8 block's centre
-// (a compile-time constant per column: no per-pixel dx or dx^2 for the
-// moments) and folds each row with dy = pixel y - splat y:
+// Moments about the wave block's centre.  A lane sums, per pixel of its
+// splat's walk, e = G dL/da against the pixel centre's offset xc from the
+// block centre (a compile-time constant per column: no per-pixel dx or dx^2
+// for the moments) and folds each row with dy = pixel y - splat y:
 //   X1 = sum e xc, X2 = sum e xc^2, XY = sum e xc dy, My = sum e dy,
 //   Myy = sum e dy^2, S = sum e.
 // With dx = xc - m (m the splat centre's offset from the block centre) the
-// moments about the splat centre follow once per block:
+// moments about the splat centre follow once per splat:
 //   Mx = X1 - m S,  Mxx = X2 - 2 m X1 + m^2 S,  Mxy = XY - m My,
 // whose rounding is bounded like that of summing e dx directly (|xc| + |m|
 // bounds |dx| over the block).
@@ -844,115 +628,301 @@ __device__ __forceinline__ void fold_row(BlockMoments& M, float dy, float S0, fl
   M.Myy = fmaf(dy * dy, S0, M.Myy);
 }
 
-// One splat's gradient sums over its pixels of the tile: with G = exp(-q/2)
-// and e = G dL/da, the moments of e about the splat's centre and sum G gbar.
-//
-// OIT (Eq. 2): plus the coverage term.  A layer's opacity alpha = u G
-// (clamped to [0, 1], no gradient where clamped) gets
-// dL/dalpha = -k / (1 - alpha) with k from pixel_factors, so per pixel
-// dq = -G (amp dL/da + u dL/dalpha) / 2, the moments carry the amplitude, and
-// there are two more sums, sum G dL/da and dL/du = sum G dL/dalpha.
-template <bool OIT>
-struct WalkSums {
-  float Mx = 0.f, My = 0.f, Mxx = 0.f, Mxy = 0.f, Myy = 0.f, S = 0.f;
-  float g_r = 0.f, g_g = 0.f, g_b = 0.f, g_amp = 0.f, g_u = 0.f;
-
-  __device__ __forceinline__ void add_block(const BlockMoments& B, float m) {
-    Mx += fmaf(-m, B.S, B.X1);
-    Mxx += fmaf(m, fmaf(m, B.S, -2.f * B.X1), B.X2);
-    Mxy += fmaf(-m, B.My, B.XY);
-    My += B.My;
-    Myy += B.Myy;
-    S += B.S;
-  }
-
-  // the sums of the lanes d apart, added
-  __device__ __forceinline__ void add_lanes(int d) {
-    float* const v[] = {&Mx, &My, &Mxx, &Mxy, &Myy, &S, &g_r, &g_g, &g_b, &g_amp, &g_u};
-#pragma unroll
-    for (int k = 0; k < (OIT ? 11 : 9); ++k) *v[k] += __shfl_xor(*v[k], d, kWave);
-  }
-};
-
-// One row of eight pixels of the walk.  dx: the row's pixel centres minus the
-// splat's, dy likewise; pd, pk: the row's per-pixel factors in LDS.  Columns
-// j and 7 - j lie at -xc and +xc from the block centre, so their e enter the
-// moments as a sum and a difference: 6 instead of 8 operations per pair.
-template <bool OIT>
-__device__ __forceinline__ void walk_row(WalkSums<OIT>& W, BlockMoments& B, const StagedRec& r, const float (&dx)[8], float dy,
-                                         float K, const float4* pd_row, const float* pk_row) {
-  const float A = r.r0.z, B2 = r.r0.w, Cc = r.r2.x;
-  const float cr = r.r1.x, cg = r.r1.y, cb = r.r1.z, amp = r.r1.w;
-  const float B2dy = B2 * dy, Cdy2 = (Cc * dy) * dy;
-  float4 pds[8];  // requested before the arithmetic below, which covers their latency
-#pragma unroll
-  for (int k = 0; k < 8; ++k) pds[k] = pd_row[k];
-  float q[8], G[8];
-#pragma unroll
-  for (int k = 0; k < 8; ++k) q[k] = quad_form(A, B2dy, Cdy2, dx[k]);
-  falloff_row(q, K, G);
-  float rc[8];  // OIT: 1 / (1 - alpha)
-  if constexpr (OIT) {
-    const float u = r.r2.z;
-    float om[8];
-#pragma unroll
-    for (int k = 0; k < 8; ++k) om[k] = fmaf(-u, G[k], 1.f);
-    // hardware reciprocal (within 1 ulp) instead of an IEEE division
-    trans_burst([&] {
-#pragma unroll
-      for (int k = 0; k < 8; ++k) rc[k] = __builtin_amdgcn_rcpf(om[k]);
-    });
-  }
-  float S0 = 0.f, S1 = 0.f, S2 = 0.f;
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const float xc = 3.5f - static_cast<float>(j);
-    float f[2];  // the factor of G in e, at columns j and 7 - j
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const int k = h ? 7 - j : j;
-      const float4 pd = pds[k];
-      const float dLda = fmaf(pd.x, cr, fmaf(pd.y, cg, fmaf(pd.z, cb, -pd.w)));
-      W.g_r = fmaf(G[k], pd.x, W.g_r);
-      W.g_g = fmaf(G[k], pd.y, W.g_g);
-      W.g_b = fmaf(G[k], pd.z, W.g_b);
-      if constexpr (OIT) {
-        const float u = r.r2.z;
-        const float al = u * G[k];
-        const float dLdal = (al > 0.f && al < 1.f) ? -pk_row[k] * rc[k] : 0.f;
-        W.g_amp = fmaf(G[k], dLda, W.g_amp);
-        W.g_u = fmaf(G[k], dLdal, W.g_u);
-        f[h] = fmaf(amp, dLda, u * dLdal);
-      } else {
-        f[h] = dLda;
-      }
-    }
-    const float eb = G[7 - j] * f[1];
-    const float sum = fmaf(G[j], f[0], eb), dif = fmaf(-G[j], f[0], eb);
-    S0 += sum;
-    S1 = fmaf(dif, xc, S1);
-    S2 = fmaf(sum, xc * xc, S2);
-  }
-  fold_row(B, dy, S0, S1, S2);
+__device__ __forceinline__ BlockMoments shfl_sum(BlockMoments M, int d) {
+  M.X1 += __shfl_xor(M.X1, d, kWave);
+  M.X2 += __shfl_xor(M.X2, d, kWave);
+  M.XY += __shfl_xor(M.XY, d, kWave);
+  M.My += __shfl_xor(M.My, d, kWave);
+  M.Myy += __shfl_xor(M.Myy, d, kWave);
+  M.S += __shfl_xor(M.S, d, kWave);
+  return M;
 }
 
-// The walk's sums as the pair's partial 2D gradient at its Gaussian-major
-// slot, with plain stores: the dq factors of the mean and conic gradients
-// (dq = -a e / 2 per pixel, with a = amp G; the staged conic is scaled by
-// log2(e) / 2, undone here), dL/dc = amp sum G gbar and dL/damp = sum G dL/da.
-// The amplitude multiplies the moments once (OIT: they carry it).
-template <bool OIT>
-__device__ __forceinline__ void walk_store(const RasterArgs& a, uint32_t slot, const WalkSums<OIT>& W,
-                                           const StagedRec& r) {
-  if (slot >= a.capacity) return;
-  const float amp = r.r1.w, A = r.r0.z, B2 = r.r0.w, Cc = r.r2.x;
-  const float ampm = OIT ? 1.f : amp, ampc = ampm * kTwoLn2;
-  float3* dst = a.part + 3 * static_cast<int64_t>(slot);
-  dst[0] = make_float3(ampc * (A * W.Mx + 0.5f * B2 * W.My), ampc * (0.5f * B2 * W.Mx + Cc * W.My),
-                       -0.5f * ampm * W.Mxx);
-  dst[1] = make_float3(-ampm * W.Mxy, -0.5f * ampm * W.Myy, amp * W.g_r);
-  dst[2] = make_float3(amp * W.g_g, amp * W.g_b, OIT ? W.g_amp : W.S);
-  if (OIT) a.du[slot] = W.g_u;
+// The five 2D-gradient sums from the block moments: the dq factors of the
+// mean and conic gradients (dq = -a e / 2 per pixel, with a = amp G; the
+// staged conic is scaled by log2(e) / 2, undone here).  `amp` multiplies the
+// sums once (1 where the moments already carry the amplitude).
+__device__ __forceinline__ void geom_sums(const BlockMoments& M, float m, float amp, float A, float B2, float Cc,
+                                          float* o) {
+  const float Mx = fmaf(-m, M.S, M.X1);
+  const float Mxx = fmaf(m, fmaf(m, M.S, -2.f * M.X1), M.X2);
+  const float Mxy = fmaf(-m, M.My, M.XY);
+  const float ampc = amp * kTwoLn2;
+  o[0] = ampc * (A * Mx + 0.5f * B2 * M.My);
+  o[1] = ampc * (0.5f * B2 * Mx + Cc * M.My);
+  o[2] = -0.5f * amp * Mxx;
+  o[3] = -amp * Mxy;
+  o[4] = -0.5f * amp * M.Myy;
+}
+
+// One chunk of the backward for one wave: up to 64 splats of the wave's
+// culled list, one per lane, each walked over the wave's 8x8 pixel block.
+// Per splat the lane sums, with G = exp(-q/2) and e = G dL/da, the block
+// moments of e (three FMAs a pixel, see BlockMoments) and sum G gbar.  The
+// splat's amplitude multiplies them once at the end.  The lane's nine
+// partial 2D gradient sums are written to out[j][lane].  A lane past the
+// end of the list gets a negative cutoff, so no pixel passes.
+//
+// All lanes walk the same pixel at the same time, so the per-pixel factors
+// (gbar, s) are read from LDS at a wave-uniform address (a broadcast).
+template <int T, bool CUT>
+__device__ __forceinline__ void bwd_chunk(const TileCtx<T>& c, int c0, int m, const uint8_t* list,
+                                          const StagedRec* s_rec, const float4* pd_wave,
+                                          float (*out)[kWave], float tau) {
+  const int j = c0 + c.lane;
+  const bool valid = j < m;
+  const int kr = valid ? list[j] : 0;
+  const StagedRec r = s_rec[kr];
+  const float amp = r.r1.y, cr = r.r1.z, cg = r.r1.w, cb = r.r2.x;
+  BlockMoments M;
+  float g_r = 0.f, g_g = 0.f, g_b = 0.f;
+  const float A = r.r0.z, B2 = r.r0.w, Cc = r.r1.x;
+  const float cut = valid ? (CUT ? r.r2.y : tau) : -1.f;
+  // first pixel centre of the block relative to the tile's centre (exact),
+  // so dx = (ex0 + col) - mx matches the forward's
+  const float ex0 = static_cast<float>(c.bx0 - c.fx0) + 0.5f;
+  const float ey0 = static_cast<float>(c.by0 - c.fy0) + 0.5f;
+  float yrow = ey0;  // this row's pixel centre (exact: ey0 + row)
+#pragma unroll 1
+  for (int row = 0; row < 8; ++row, yrow += 1.f) {
+    const float dy = yrow - r.r0.y;
+    const float B2dy = B2 * dy, Cdy2 = (Cc * dy) * dy;
+    float S0 = 0.f, S1 = 0.f, S2 = 0.f;
+#pragma unroll
+    for (int col = 0; col < 8; ++col) {
+      const float xc = static_cast<float>(col) - 3.5f;
+      const float dx = (ex0 + static_cast<float>(col)) - r.r0.x;
+      const float q = quad_form(A, B2dy, Cdy2, dx);
+      const float4 pd = pd_wave[row * 8 + col];  // wave-uniform LDS address: a broadcast read
+      const float Gq = q <= cut ? falloff(q) : 0.f;
+      const float dLda = fmaf(pd.x, cr, fmaf(pd.y, cg, fmaf(pd.z, cb, -pd.w)));
+      const float e = Gq * dLda;
+      S0 += e;
+      S1 = fmaf(e, xc, S1);
+      S2 = fmaf(e, xc * xc, S2);
+      g_r = fmaf(Gq, pd.x, g_r);
+      g_g = fmaf(Gq, pd.y, g_g);
+      g_b = fmaf(Gq, pd.z, g_b);
+    }
+    fold_row(M, dy, S0, S1, S2);
+  }
+  // dL/dc = amp sum G gbar, dL/damp = sum G dL/da
+  const int l = c.lane;
+  float o[5];
+  geom_sums(M, r.r0.x - (ex0 + 3.5f), amp, A, B2, Cc, o);
+#pragma unroll
+  for (int q = 0; q < 5; ++q) out[q][l] = o[q];
+  out[5][l] = amp * g_r;
+  out[6][l] = amp * g_g;
+  out[7][l] = amp * g_b;
+  out[8][l] = M.S;
+}
+
+// A short chunk (at most 64 / K splats, K = 2, 4 or 8), which would leave
+// most lanes of bwd_chunk idle: K lanes share a splat, lane group g walking
+// rows [g 8/K, (g+1) 8/K) of the block, and the groups' sums are added with
+// cross-lane shuffles in a fixed order.  The groups visit different pixels
+// at the same time, so the per-pixel factors come from this wave's copy in
+// LDS (s_pd, 64 entries) at per-group addresses.  The arithmetic per pixel
+// is that of bwd_chunk.
+template <int T, bool CUT, int K>
+__device__ __forceinline__ void bwd_chunk_split(const TileCtx<T>& c, int c0, int m, const uint8_t* list,
+                                                const StagedRec* s_rec, const float4* s_pd, float (*out)[kWave],
+                                                float tau) {
+  constexpr int S = kWave / K;  // splats per chunk
+  constexpr int R = 8 / K;      // rows per lane group
+  const int g = c.lane / S;
+  const int slot = c.lane % S;
+  const int j = c0 + slot;
+  const bool valid = j < m;
+  const int kr = valid ? list[j] : 0;
+  const StagedRec r = s_rec[kr];
+  const float amp = r.r1.y, cr = r.r1.z, cg = r.r1.w, cb = r.r2.x;
+  BlockMoments M;
+  float g_r = 0.f, g_g = 0.f, g_b = 0.f;
+  const float A = r.r0.z, B2 = r.r0.w, Cc = r.r1.x;
+  const float cut = valid ? (CUT ? r.r2.y : tau) : -1.f;
+  const float ex0 = static_cast<float>(c.bx0 - c.fx0) + 0.5f;
+  const float ey0 = static_cast<float>(c.by0 - c.fy0 + g * R) + 0.5f;  // first row of this group
+  const float4* pd_rows = s_pd + g * R * 8;
+#pragma unroll
+  for (int row = 0; row < R; ++row) {
+    const float dy = (ey0 + static_cast<float>(row)) - r.r0.y;
+    const float B2dy = B2 * dy, Cdy2 = (Cc * dy) * dy;
+    float S0 = 0.f, S1 = 0.f, S2 = 0.f;
+#pragma unroll
+    for (int col = 0; col < 8; ++col) {
+      const float xc = static_cast<float>(col) - 3.5f;
+      const float dx = (ex0 + static_cast<float>(col)) - r.r0.x;
+      const float q = quad_form(A, B2dy, Cdy2, dx);
+      const float4 pd = pd_rows[row * 8 + col];
+      const float Gq = q <= cut ? falloff(q) : 0.f;
+      const float dLda = fmaf(pd.x, cr, fmaf(pd.y, cg, fmaf(pd.z, cb, -pd.w)));
+      const float e = Gq * dLda;
+      S0 += e;
+      S1 = fmaf(e, xc, S1);
+      S2 = fmaf(e, xc * xc, S2);
+      g_r = fmaf(Gq, pd.x, g_r);
+      g_g = fmaf(Gq, pd.y, g_g);
+      g_b = fmaf(Gq, pd.z, g_b);
+    }
+    fold_row(M, dy, S0, S1, S2);
+  }
+#pragma unroll
+  for (int d = S; d < kWave; d <<= 1) {
+    M = shfl_sum(M, d);
+    g_r += __shfl_xor(g_r, d, kWave);
+    g_g += __shfl_xor(g_g, d, kWave);
+    g_b += __shfl_xor(g_b, d, kWave);
+  }
+  if (g == 0) {
+    float o[5];
+    geom_sums(M, r.r0.x - (ex0 + 3.5f), amp, A, B2, Cc, o);
+#pragma unroll
+    for (int q = 0; q < 5; ++q) out[q][slot] = o[q];
+    out[5][slot] = amp * g_r;
+    out[6][slot] = amp * g_g;
+    out[7][slot] = amp * g_b;
+    out[8][slot] = M.S;
+  }
+}
+
+// The OIT chunk (Eq. 2): as bwd_chunk, plus the coverage term.  A layer's
+// opacity alpha = u G (clamped to [0, 1], no gradient where clamped) gets
+// dL/dalpha = -k / (1 - alpha) with k from pixel_factors, so per pixel
+// dq = -G (amp dL/da + u dL/dalpha) / 2, and the tenth output is
+// dL/du = sum G dL/dalpha.  The moments therefore carry the amplitude.
+template <int T>
+__device__ __forceinline__ void bwd_chunk_oit(const TileCtx<T>& c, int c0, int m, const uint8_t* list,
+                                              const StagedRec* s_rec,
+                                              const float4* pd_wave, const float* pk_wave,
+                                              float (*out)[kWave], float tau) {
+  const int j = c0 + c.lane;
+  const bool valid = j < m;
+  const int kr = valid ? list[j] : 0;
+  const StagedRec r = s_rec[kr];
+  const float u = r.r2.z;
+  const float amp = r.r1.y, cr = r.r1.z, cg = r.r1.w, cb = r.r2.x;
+  BlockMoments M;
+  float g_r = 0.f, g_g = 0.f, g_b = 0.f, g_amp = 0.f, g_u = 0.f;
+  const float A = r.r0.z, B2 = r.r0.w, Cc = r.r1.x;
+  const float cut = valid ? tau : -1.f;
+  const float ex0 = static_cast<float>(c.bx0 - c.fx0) + 0.5f;
+  const float ey0 = static_cast<float>(c.by0 - c.fy0) + 0.5f;
+  float yrow = ey0;  // this row's pixel centre (exact: ey0 + row)
+#pragma unroll 1
+  for (int row = 0; row < 8; ++row, yrow += 1.f) {
+    const float dy = yrow - r.r0.y;
+    const float B2dy = B2 * dy, Cdy2 = (Cc * dy) * dy;
+    float S0 = 0.f, S1 = 0.f, S2 = 0.f;
+#pragma unroll
+    for (int col = 0; col < 8; ++col) {
+      const float xc = static_cast<float>(col) - 3.5f;
+      const float dx = (ex0 + static_cast<float>(col)) - r.r0.x;
+      const float q = quad_form(A, B2dy, Cdy2, dx);
+      const float4 pd = pd_wave[row * 8 + col];  // wave-uniform LDS address: a broadcast read
+      const float k = pk_wave[row * 8 + col];
+      const float Gq = q <= cut ? falloff(q) : 0.f;
+      const float dLda = fmaf(pd.x, cr, fmaf(pd.y, cg, fmaf(pd.z, cb, -pd.w)));
+      const float al = u * Gq;
+      // hardware reciprocal (within 1 ulp) instead of an IEEE division
+      const float dLdal = (al > 0.f && al < 1.f) ? -k * __builtin_amdgcn_rcpf(1.f - al) : 0.f;
+      const float e = Gq * fmaf(amp, dLda, u * dLdal);
+      S0 += e;
+      S1 = fmaf(e, xc, S1);
+      S2 = fmaf(e, xc * xc, S2);
+      g_r = fmaf(Gq, pd.x, g_r);
+      g_g = fmaf(Gq, pd.y, g_g);
+      g_b = fmaf(Gq, pd.z, g_b);
+      g_amp = fmaf(Gq, dLda, g_amp);
+      g_u = fmaf(Gq, dLdal, g_u);
+    }
+    fold_row(M, dy, S0, S1, S2);
+  }
+  const int l = c.lane;
+  float o[5];
+  geom_sums(M, r.r0.x - (ex0 + 3.5f), 1.f, A, B2, Cc, o);
+#pragma unroll
+  for (int q = 0; q < 5; ++q) out[q][l] = o[q];
+  out[5][l] = amp * g_r;
+  out[6][l] = amp * g_g;
+  out[7][l] = amp * g_b;
+  out[8][l] = g_amp;
+  out[9][l] = g_u;
+}
+
+// bwd_chunk_oit for a short chunk, with K lanes per splat as in
+// bwd_chunk_split (per-pixel factors and coverage factors from LDS).
+template <int T, int K>
+__device__ __forceinline__ void bwd_chunk_oit_split(const TileCtx<T>& c, int c0, int m, const uint8_t* list,
+                                                    const StagedRec* s_rec, const float4* s_pd,
+                                                    const float* s_pk, float (*out)[kWave], float tau) {
+  constexpr int S = kWave / K;  // splats per chunk
+  constexpr int R = 8 / K;      // rows per lane group
+  const int g = c.lane / S;
+  const int slot = c.lane % S;
+  const int j = c0 + slot;
+  const bool valid = j < m;
+  const int kr = valid ? list[j] : 0;
+  const StagedRec r = s_rec[kr];
+  const float u = r.r2.z;
+  const float amp = r.r1.y, cr = r.r1.z, cg = r.r1.w, cb = r.r2.x;
+  BlockMoments M;
+  float g_r = 0.f, g_g = 0.f, g_b = 0.f, g_amp = 0.f, g_u = 0.f;
+  const float A = r.r0.z, B2 = r.r0.w, Cc = r.r1.x;
+  const float cut = valid ? tau : -1.f;
+  const float ex0 = static_cast<float>(c.bx0 - c.fx0) + 0.5f;
+  const float ey0 = static_cast<float>(c.by0 - c.fy0 + g * R) + 0.5f;  // first row of this group
+  const float4* pd_rows = s_pd + g * R * 8;
+  const float* pk_rows = s_pk + g * R * 8;
+#pragma unroll
+  for (int row = 0; row < R; ++row) {
+    const float dy = (ey0 + static_cast<float>(row)) - r.r0.y;
+    const float B2dy = B2 * dy, Cdy2 = (Cc * dy) * dy;
+    float S0 = 0.f, S1 = 0.f, S2 = 0.f;
+#pragma unroll
+    for (int col = 0; col < 8; ++col) {
+      const float xc = static_cast<float>(col) - 3.5f;
+      const float dx = (ex0 + static_cast<float>(col)) - r.r0.x;
+      const float q = quad_form(A, B2dy, Cdy2, dx);
+      const float4 pd = pd_rows[row * 8 + col];
+      const float k = pk_rows[row * 8 + col];
+      const float Gq = q <= cut ? falloff(q) : 0.f;
+      const float dLda = fmaf(pd.x, cr, fmaf(pd.y, cg, fmaf(pd.z, cb, -pd.w)));
+      const float al = u * Gq;
+      const float dLdal = (al > 0.f && al < 1.f) ? -k * __builtin_amdgcn_rcpf(1.f - al) : 0.f;
+      const float e = Gq * fmaf(amp, dLda, u * dLdal);
+      S0 += e;
+      S1 = fmaf(e, xc, S1);
+      S2 = fmaf(e, xc * xc, S2);
+      g_r = fmaf(Gq, pd.x, g_r);
+      g_g = fmaf(Gq, pd.y, g_g);
+      g_b = fmaf(Gq, pd.z, g_b);
+      g_amp = fmaf(Gq, dLda, g_amp);
+      g_u = fmaf(Gq, dLdal, g_u);
+    }
+    fold_row(M, dy, S0, S1, S2);
+  }
+#pragma unroll
+  for (int d = S; d < kWave; d <<= 1) {
+    M = shfl_sum(M, d);
+    g_r += __shfl_xor(g_r, d, kWave);
+    g_g += __shfl_xor(g_g, d, kWave);
+    g_b += __shfl_xor(g_b, d, kWave);
+    g_amp += __shfl_xor(g_amp, d, kWave);
+    g_u += __shfl_xor(g_u, d, kWave);
+  }
+  if (g == 0) {
+    float o[5];
+    geom_sums(M, r.r0.x - (ex0 + 3.5f), 1.f, A, B2, Cc, o);
+#pragma unroll
+    for (int q = 0; q < 5; ++q) out[q][slot] = o[q];
+    out[5][slot] = amp * g_r;
+    out[6][slot] = amp * g_g;
+    out[7][slot] = amp * g_b;
+    out[8][slot] = g_amp;
+    out[9][slot] = g_u;
+  }
 }
 
 // The backward's per-pixel factors for pixel (px, py) of view `cam`:
@@ -1008,265 +978,152 @@ __device__ __forceinline__ void pixel_factors(const RasterArgs& a, const DevCame
   *kcov_o = kcov;
 }
 
-// A backward workgroup has four waves whatever the tile size, and the compiler
-// is asked for four resident waves per SIMD, as many as the SIMD needs to issue
-// two FP32 operations at once throughout (at most 128 VGPRs).
-constexpr int kBwdWaves = 4;
-constexpr int kBwdThreads = kBwdWaves * kWave;
-// Backward of one work item.  Every lane takes one splat of the item and walks
-// the sub-blocks of the tile that its support reaches, so a splat's
-// gradient sums stay in its lane's registers from the first pixel to the
-// store: no merging between waves, and no barrier, once the walk has begun.
-// The lanes of a wave walk the sub-blocks of their own splats (a lane's j-th
-// is its splat's j-th); for them to finish together the item's splats are
-// first sorted by the number of sub-blocks they reach (a counting sort in LDS),
-// the most first.  Splats that reach none get zeros.  The records of a
-// wave's next splats are requested before it walks the present ones.
+// Tile 16 asks the compiler for five resident waves per SIMD with Eq. 7 (at
+// most 102 VGPRs): the short-chunk path would otherwise raise the register
+// count and cost a wave.  With Eq. 2 it asks for four (at most 128 VGPRs, no
+// spills; the unbounded kernel takes 165, three waves): five would fit the
+// LDS but spill 19 registers, which measured slower.
+template <int T, bool OIT>
+constexpr int bwd_min_blocks() {
+  return T == 16 ? (OIT ? 4 : 5) : 1;
+}
+
+// Backward: each thread first forms its pixel's factors (pixel_factors)
+// into LDS; the tile's first work item also stores the tile's
+// background-gradient partial sums.  Then the same staging and per-wave
+// culling as the forward, but lanes own splats of the wave's culled list and
+// walk the wave's pixel block (see bwd_chunk), so a splat's nine gradient
+// sums stay in registers.  A chunk of at most 32 splats (the tail of a
+// wave's list) shares each splat among 2, 4 or 8 lanes instead
+// (bwd_chunk_split, bwd_chunk_oit_split).
 //
-// The previous form (waves owning blocks, lanes owning splats of the wave's
-// culled list, the waves' sums merged through LDS in lockstep rounds) spent
-// 47 % of its wave time waiting at the rounds' barriers, at the staging's and
-// on LDS.
-//
-// The last splats, fewer than the workgroup has lanes, are shared by W = 1, 2,
-// 4 or 8 lanes each, which split the rows of every sub-block (and, where it
-// has fewer rows than W, the sub-blocks); the lanes' sums are added with
-// shuffles.  A splat's sums
-// depend on its place in the sort through W alone, and the sort is stable, so
-// they do not vary from run to run.
-template <int T>
-struct BwdShared {
-  // the item's splats, most sub-blocks first: Gaussian id; index in the item,
-  // and in the upper half the sub-blocks it reaches (one bit each)
-  uint2 order[kItemSplats];
-  uint32_t count[TileGeom<T>::kSubs + 1][kBwdWaves];  // per number of sub-blocks and wave
-};
-
-// Wave w sorts the w-th share of the item, whole groups of 64 splats.  All
-// global loads of the sort are issued by bwd_sort_begin, so that they and the
-// pixel factors' cost one memory round trip.
-template <int T>
-struct BwdShare {
-  static constexpr int kGroups = kItemSplats / kBwdThreads;
-  int w0, w1;              // the share, relative to the item
-  uint32_t id[kGroups];    // of each group's entry: the Gaussian
-  uint32_t hits[kGroups];  // and the sub-blocks it reaches
-};
-
-template <int T, bool CUT, bool OIT>
-__device__ __forceinline__ void bwd_sort_begin(const RasterArgs& a, const TileCtx<T>& c, BwdShare<T>& q,
-                                               const HitBits<T>* masks_in) {
-  using G = TileGeom<T>;
-  const int len = static_cast<int>(c.end - c.start);
-  const int per = ((len + kBwdWaves - 1) / kBwdWaves + kWave - 1) & ~(kWave - 1);
-  q.w0 = min(c.wave * per, len);
-  q.w1 = min(q.w0 + per, len);
-#pragma unroll
-  for (int g = 0; g < BwdShare<T>::kGroups; ++g) {
-    const int e = q.w0 + g * kWave + c.lane;
-    q.id[g] = e < q.w1 ? a.ent[c.start + e].x : 0u;
-    q.hits[g] = masks_in && e < q.w1 ? masks_in[c.start + e] : 0u;
-  }
-  if (!masks_in) {
-#pragma unroll
-    for (int g = 0; g < BwdShare<T>::kGroups; ++g) {
-      const int e = q.w0 + g * kWave + c.lane;
-      if (e < q.w1)
-        q.hits[g] = sub_hits<T, G::kSubs, CUT>(
-            make_staged<CUT, OIT, false>(a.rec + static_cast<int64_t>(c.v) * c.n + q.id[g],
-                                         static_cast<float>(c.fx0), static_cast<float>(c.fy0)),
-            a.tau, true, 0);
-    }
-  }
-}
-
-template <int T>
-__device__ __forceinline__ int bwd_sort(const TileCtx<T>& c, BwdShare<T>& q, BwdShared<T>& sh) {
-  using G = TileGeom<T>;
-  constexpr int NB = G::kSubs;
-  constexpr int NG = BwdShare<T>::kGroups;
-  uint32_t at[NB + 1];  // per number of sub-blocks: this wave's splats, then the place of its next one
-#pragma unroll
-  for (int k = 0; k <= NB; ++k) at[k] = 0;
-#pragma unroll
-  for (int g = 0; g < NG; ++g) {
-    if (q.w0 + g * kWave >= q.w1) break;
-    const int n = q.w0 + g * kWave + c.lane < q.w1 ? __popc(q.hits[g]) : -1;
-#pragma unroll
-    for (int k = 0; k <= NB; ++k) at[k] += static_cast<uint32_t>(__popcll(__ballot(n == k)));
-  }
-  if (c.lane == 0) {
-#pragma unroll
-    for (int k = 0; k <= NB; ++k) sh.count[k][c.wave] = at[k];
-  }
-  lds_barrier();
-  int total = 0, reaching = 0;
-#pragma unroll
-  for (int k = NB; k >= 0; --k) {
-    if (k == 0) reaching = total;
-#pragma unroll
-    for (int w = 0; w < kBwdWaves; ++w) {
-      if (w == c.wave) at[k] = static_cast<uint32_t>(total);
-      total += static_cast<int>(sh.count[k][w]);
-    }
-  }
-#pragma unroll
-  for (int g = 0; g < NG; ++g) {
-    if (q.w0 + g * kWave >= q.w1) break;
-    const int e = q.w0 + g * kWave + c.lane;
-    const uint32_t h = q.hits[g];
-    const int n = e < q.w1 ? __popc(h) : -1;
-    uint32_t place = 0;
-#pragma unroll
-    for (int k = 0; k <= NB; ++k) {
-      const uint64_t same = __ballot(n == k);
-      if (n == k) place = at[k] + static_cast<uint32_t>(__popcll(same & ((1ull << c.lane) - 1ull)));
-      at[k] += static_cast<uint32_t>(__popcll(same));
-    }
-    if (n >= 0) sh.order[place] = make_uint2(q.id[g], static_cast<uint32_t>(e) | (h << 16));
-  }
-  lds_barrier();
-  return reaching;
-}
-
-// Walk the splats of a wave, W lanes each.  order: index in the item, and in
-// the upper half the sub-blocks the splat reaches (0: no splat).
-template <int T, bool CUT, bool OIT, int W>
-__device__ __forceinline__ void bwd_walk(const RasterArgs& a, const TileCtx<T>& c, const float4* s_pd,
-                                         const float* s_pk, const StagedRec& r, uint32_t order) {
-  using G = TileGeom<T>;
-  constexpr int S = kWave / W;                       // splats per wave
-  constexpr int WR = W < G::kRows ? W : G::kRows;    // lanes that share a sub-block's rows
-  constexpr int R = G::kRows / WR;                   // rows per lane
-  const int g = c.lane / S;
-  uint32_t h = order >> 16;
-  const bool valid = h != 0;
-  if (W > WR) h &= g / WR == 0 ? 0x5555u : 0xaaaau;  // two lanes share the sub-blocks
-  const uint32_t slot = a.ent[c.start + (order & 0xffffu)].y;  // needed at the end only
-  const float Kv = CUT ? r.r2.w : support_k(a.tau);
-  WalkSums<OIT> sums;
-  while (__any(h != 0)) {
-    const float K = h != 0 ? Kv : support_k(-1.f);
-    const int b = h != 0 ? __ffs(static_cast<int>(h)) - 1 : 0;
-    h &= h - 1u;
-    // the first pixel centre relative to the tile's centre (exact, so that dx
-    // and dy match the forward's)
-    const float ex0 = G::sub_x(b);
-    float yrow = G::sub_y(b) + static_cast<float>(g % WR * R);
-    float dx[8];
-#pragma unroll
-    for (int k = 0; k < 8; ++k) dx[k] = (ex0 + static_cast<float>(k)) - r.r0.x;
-    const int at = b * kPdStride<T> + g % WR * R * 8;
-    const float4* pd = s_pd + at;
-    const float* pk = OIT ? s_pk + at : nullptr;
-    BlockMoments B;
-#pragma unroll 1
-    for (int row = 0; row < R; ++row, yrow += 1.f)
-      walk_row<OIT>(sums, B, r, dx, yrow - r.r0.y, K, pd + row * 8, OIT ? pk + row * 8 : nullptr);
-    sums.add_block(B, r.r0.x - (ex0 + 3.5f));
-  }
-#pragma unroll
-  for (int d = S; d < kWave; d <<= 1) sums.add_lanes(d);
-  if (g == 0 && valid) walk_store<OIT>(a, slot, sums, r);
-}
-
-template <int T, bool CUT, bool OIT, bool PERSIST>
-__global__ __launch_bounds__(kBwdThreads, 4) void raster_bwd_kernel(
+// The waves of a tile merge their sums without atomics.  Thread k owns
+// staged record k.  The waves process their chunks in lockstep rounds (one
+// chunk each per round); after a round every wave's sums sit in LDS, and each
+// owner adds the entries of its record -- found through the per-wave list
+// positions recorded by the culling -- into registers, waves in a fixed
+// order.  At the end of the batch the owner stores the record's sums, zeros
+// included, with plain stores at the pair's Gaussian-major slot.  For given
+// tile lists the summation order is fixed, so the result does not vary from
+// run to run (the order in which a record's per-wave sums are added follows
+// the rounds that reach them, i.e. the list positions).
+template <int T, int S, bool CUT, bool OIT, bool PERSIST>
+__global__ __launch_bounds__(TileGeom<T>::kThreads, (bwd_min_blocks<T, OIT>())) void raster_bwd_kernel(
     RasterArgs a) {
   using G = TileGeom<T>;
-  __shared__ BwdShared<T> sh;
-  __shared__ float4 s_pd[G::kSubs * kPdStride<T>];            // per-pixel factors, sub-block by sub-block
-  __shared__ float s_pk[OIT ? G::kSubs * kPdStride<T> : 1];   // OIT: per-pixel coverage factors
-  __shared__ float s_bg[kBwdWaves][4];
+  constexpr int kB = S;  // records staged per batch (thread k < kB owns record k)
+  static_assert(kB <= G::kThreads, "every staged record needs an owner thread");
+  static_assert(kB <= 256, "the culled lists hold 8-bit record indices");
+  constexpr int NV = OIT ? 10 : 9;  // sums per (tile, splat) pair
+  __shared__ StagedRec s_rec[kB];
+  __shared__ uint32_t s_slot[kB];
+  __shared__ __align__(16) uint8_t s_list[G::kWaves * kB];
+  __shared__ uint16_t s_pos[G::kWaves * kB];
+  __shared__ float s_part[G::kWaves][NV][kWave];
+  __shared__ int s_m[G::kWaves];
+  __shared__ float4 s_pd[G::kThreads];            // per-pixel factors, thread order
+  __shared__ float s_pk[OIT ? G::kThreads : 1];   // OIT: per-pixel coverage factors
+  __shared__ float s_bg[G::kWaves][4];
   __shared__ uint32_t s_item;
   // the forward's culling masks, if it stored them for these lists with the
   // same early-out setting
-  const HitBits<T>* masks_in = (a.masks && a.flags->cull_masks == (kCullMasks | (CUT ? 2u : 0u)))
-                                   ? static_cast<const HitBits<T>*>(a.masks) : nullptr;
+  const uint64_t* masks_in =
+      (a.masks && a.flags->cull_masks == (kCullMasks | (CUT ? 2u : 0u))) ? a.masks : nullptr;
   const uint32_t n_items = a.items[a.total_tiles];
   uint32_t item = PERSIST ? claim_item(a, &s_item) : blockIdx.x;
   while (item < n_items) {
     TileCtx<T> c;
     const DevCamera* cam;
     tile_setup<T>(a, item, c, cam);
-    BwdShare<T> share;
-    bwd_sort_begin<T, CUT, OIT>(a, c, share, masks_in);
-    // every thread's pixel factors into LDS; the tile's first work item also
-    // stores the tile's background-gradient partial sums
+
+    // every thread's per-pixel factors into LDS, where the chunks read them at
+    // wave-uniform (broadcast) or per-lane addresses; the tile's first work
+    // item also stores the tile's background-gradient partial sums
     {
-      float back[4] = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int p = threadIdx.x; p < T * T; p += kBwdThreads) {
-        const int sub = p / (G::kRows * 8), at = p % (G::kRows * 8);  // pixel `at` of a sub-block
-        float4 pd;
-        float kcov, bacc[4];
-        pixel_factors<OIT>(a, *cam, c.tx * T + sub / G::kHalves % (T / 8) * 8 + (at & 7),
-                           c.ty * T + sub / G::kHalves / (T / 8) * 8 + sub % G::kHalves * G::kRows + (at >> 3), &pd,
-                           &kcov, bacc);
-        s_pd[sub * kPdStride<T> + at] = pd;
-        if (OIT) s_pk[sub * kPdStride<T> + at] = kcov;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) back[j] += bacc[j];
-      }
+      float4 pd;
+      float kcov, bacc[4];
+      pixel_factors<OIT>(a, *cam, c.px, c.py, &pd, &kcov, bacc);
+      s_pd[threadIdx.x] = pd;
+      if (OIT) s_pk[threadIdx.x] = kcov;
       if (c.k == 0) {
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-          const float sj = wave_sum(back[j]);
+          const float sj = wave_sum(bacc[j]);
           if (c.lane == 0) s_bg[c.wave][j] = sj;
+        }
+        __syncthreads();
+        if (threadIdx.x < 4) {
+          float sj = 0.f;
+#pragma unroll
+          for (int w = 0; w < G::kWaves; ++w) sj += s_bg[w][threadIdx.x];
+          a.tilepart[c.tile * 4 + threadIdx.x] = sj;
         }
       }
     }
-    const int n = bwd_sort<T>(c, share, sh);
-    if (c.k == 0 && threadIdx.x < 4) {
-      float sj = 0.f;
+    const float4* pd_wave = s_pd + c.wave * kWave;
+    const float* pk_wave = OIT ? s_pk + c.wave * kWave : nullptr;
+    const float tau = a.tau;
+    const int own = threadIdx.x;  // staged record owned by this thread (if < kB)
+    for (uint32_t b = c.start; b < c.end; b += kB) {
+      const int m = stage_and_cull<T, kB, true, CUT, OIT, false, uint8_t>(a, c, b, s_rec, s_slot, s_list, s_pos,
+                                                                          nullptr, masks_in);
+      const int cnt = static_cast<int>(min(static_cast<uint32_t>(kB), c.end - b));
+      if (c.lane == 0) s_m[c.wave] = m;
+      __syncthreads();
+      int rounds = 0;
 #pragma unroll
-      for (int w = 0; w < kBwdWaves; ++w) sj += s_bg[w][threadIdx.x];
-      a.tilepart[c.tile * 4 + threadIdx.x] = sj;
-    }
-    // rounds of one lane per splat that keep every wave busy, then the rest
-    // with W lanes per splat
-    const int rounds = n / kBwdThreads, rest = n % kBwdThreads;
-    const int wsh = rest * 8 <= kBwdThreads ? 3 : rest * 4 <= kBwdThreads ? 2 : rest * 2 <= kBwdThreads ? 1 : 0;
-    const DevSplat* recs = a.rec + static_cast<int64_t>(c.v) * c.n;
-    const float tox = static_cast<float>(c.fx0), toy = static_cast<float>(c.fy0);
-    // this lane's splat of a round (its record, and item index and blocks; no
-    // blocks past the end)
-    auto fetch = [&](int round, uint32_t& order, StagedRec& r) {
-      const int first = round < rounds ? round * kBwdThreads + c.wave * kWave
-                                       : rounds * kBwdThreads + c.wave * (kWave >> wsh);
-      const int j = first + (round < rounds ? c.lane : c.lane & ((kWave >> wsh) - 1));
-      const uint2 o = sh.order[min(j, n - 1)];
-      order = j < n ? o.y : o.y & 0xffffu;
-      r = make_staged<CUT, OIT, false>(recs + o.x, tox, toy);
-    };
-    if (n > 0) {
-      uint32_t o;
-      StagedRec r;
-      fetch(0, o, r);
-      for (int round = 0; round < rounds; ++round) {
-        uint32_t on;
-        StagedRec rn;
-        fetch(round + 1, on, rn);
-        bwd_walk<T, CUT, OIT, 1>(a, c, s_pd, s_pk, r, o);
-        o = on;
-        r = rn;
+      for (int w = 0; w < G::kWaves; ++w) rounds = max(rounds, (s_m[w] + kWave - 1) / kWave);
+      const uint8_t* list = s_list + c.wave * kB;
+      float acc[NV];
+#pragma unroll
+      for (int q = 0; q < NV; ++q) acc[q] = 0.f;
+      for (int r = 0; r < rounds; ++r) {
+        const int left = m - r * kWave;  // splats in this wave's chunk of the round
+        if (left > 0) {
+          const float4* pdl = pd_wave;
+          if (OIT) {
+            const float* pkl = pk_wave;
+            if (left > kWave / 2)
+              bwd_chunk_oit<T>(c, r * kWave, m, list, s_rec, pd_wave, pk_wave, s_part[c.wave], tau);
+            else if (left > kWave / 4)
+              bwd_chunk_oit_split<T, 2>(c, r * kWave, m, list, s_rec, pdl, pkl, s_part[c.wave], tau);
+            else if (left > kWave / 8)
+              bwd_chunk_oit_split<T, 4>(c, r * kWave, m, list, s_rec, pdl, pkl, s_part[c.wave], tau);
+            else
+              bwd_chunk_oit_split<T, 8>(c, r * kWave, m, list, s_rec, pdl, pkl, s_part[c.wave], tau);
+          } else {
+            if (left > kWave / 2)
+              bwd_chunk<T, CUT>(c, r * kWave, m, list, s_rec, pd_wave, s_part[c.wave], tau);
+            else if (left > kWave / 4)
+              bwd_chunk_split<T, CUT, 2>(c, r * kWave, m, list, s_rec, pdl, s_part[c.wave], tau);
+            else if (left > kWave / 8)
+              bwd_chunk_split<T, CUT, 4>(c, r * kWave, m, list, s_rec, pdl, s_part[c.wave], tau);
+            else
+              bwd_chunk_split<T, CUT, 8>(c, r * kWave, m, list, s_rec, pdl, s_part[c.wave], tau);
+          }
+        }
+        __syncthreads();
+        if (own < cnt) {
+#pragma unroll
+          for (int w = 0; w < G::kWaves; ++w) {
+            const int p = s_pos[w * kB + own];  // 0xffff: culled by wave w
+            if ((p >> 6) == r) {
+#pragma unroll
+              for (int q = 0; q < NV; ++q) acc[q] += s_part[w][q][p & (kWave - 1)];
+            }
+          }
+        }
+        __syncthreads();
       }
-      if (wsh == 3)
-        bwd_walk<T, CUT, OIT, 8>(a, c, s_pd, s_pk, r, o);
-      else if (wsh == 2)
-        bwd_walk<T, CUT, OIT, 4>(a, c, s_pd, s_pk, r, o);
-      else if (wsh == 1)
-        bwd_walk<T, CUT, OIT, 2>(a, c, s_pd, s_pk, r, o);
-      else
-        bwd_walk<T, CUT, OIT, 1>(a, c, s_pd, s_pk, r, o);
-    }
-    // the splats that reach no pixel of the tile: zeros
-    for (int j = n + threadIdx.x; j < static_cast<int>(c.end - c.start); j += kBwdThreads) {
-      const uint32_t slot = a.ent[c.start + (sh.order[j].y & 0xffffu)].y;
-      if (slot < a.capacity) {
-        float3* dst = a.part + 3 * static_cast<int64_t>(slot);
-        dst[0] = dst[1] = dst[2] = make_float3(0.f, 0.f, 0.f);
-        if (OIT) a.du[slot] = 0.f;
+      if (own < cnt) {
+        const uint32_t sl = s_slot[own];
+        if (sl < a.capacity) {
+          float3* dst = a.part + 3 * static_cast<int64_t>(sl);
+          dst[0] = make_float3(acc[0], acc[1], acc[2]);
+          dst[1] = make_float3(acc[3], acc[4], acc[5]);
+          dst[2] = make_float3(acc[6], acc[7], acc[8]);
+          if (OIT) a.du[sl] = acc[NV - 1];
+        }
       }
     }
     if (!PERSIST) break;
@@ -1278,6 +1135,19 @@ __global__ __launch_bounds__(kBwdThreads, 4) void raster_bwd_kernel(
 // sort from.  The splats are those of the weighted sum (projected with the
 // DIR weight, so a record's amplitude is the opacity u), ordered per tile by
 // camera depth and composited front to back.
+
+// Barrier between LDS writes and reads of a workgroup.  __syncthreads would
+// also wait for the outstanding global stores and loads.
+__device__ __forceinline__ void lds_barrier() {
+  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
+
+// LDS writes of this wave before, LDS reads of this wave after.
+__device__ __forceinline__ void lds_wave_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
 
 // The per-tile sort.  A list is spread over equal steps of its depth range,
 // about as many buckets as entries (counted and placed with LDS atomics), and
@@ -1589,17 +1459,18 @@ __global__ __launch_bounds__(TileGeom<T>::kThreads) void raster_sorted_kernel(Ra
   const float pcy = static_cast<float>(c.py - c.fy0) + 0.5f;
   const float tau = a.tau;
   for (uint32_t b = c.start; b < c.end; b += G::kBatch) {
-    const int m = stage_and_cull<T, G::kBatch>(a, c, b, s_rec, s_list);
+    const int m = stage_and_cull<T, G::kBatch, false, false, false, false, uint8_t>(a, c, b, s_rec, nullptr, s_list,
+                                                                            nullptr);
     const uint8_t* list = s_list + c.wave * G::kBatch;
     for (int i = 0; i < m && live; ++i) {
       const StagedRec r = s_rec[list[i]];
       const float q = pair_q(r, pcx, pcy);
-      const float al = fminf(alpha_max, r.r1.w * falloff(q));
+      const float al = fminf(alpha_max, r.r1.y * falloff(q));
       if (q <= tau && al >= alpha_min) {
         const float w = al * Tr;
-        cr = fmaf(w, r.r1.x, cr);
-        cg = fmaf(w, r.r1.y, cg);
-        cb = fmaf(w, r.r1.z, cb);
+        cr = fmaf(w, r.r1.z, cr);
+        cg = fmaf(w, r.r1.w, cg);
+        cb = fmaf(w, r.r2.x, cb);
         Tr *= 1.f - al;
         if (Tr < t_min) live = false;
       }
@@ -1645,7 +1516,13 @@ RasterArgs make_args(const Layout& L, void* ws, const void* pairs, int64_t capac
   a.acclog = at<float>(ws, L.off_acclog);
   a.du = pv.du;
   a.flags = at<DevFlags>(ws, L.off_flags);
-  a.masks = capacity > 0 ? pv.masks : nullptr;
+  // The culling masks have 4 bytes per pair of the pair buffer; a capacity
+  // too small for the per-tile rounding of the groups leaves them off.
+  {
+    const int64_t waves = static_cast<int64_t>(L.tile / 8) * (L.tile / 8);
+    const int64_t words = (((capacity + 63) >> 6) + L.total_tiles + 2) * waves;
+    a.masks = capacity > 0 && 8 * words <= 4 * capacity ? pv.masks : nullptr;
+  }
   return a;
 }
 
@@ -1711,20 +1588,20 @@ hipError_t fwd_ts(const RasterArgs& a, int64_t grid, bool count, bool cut, bool 
   return count ? fwd_k<T, S, true, false, false>(a, grid, queue, st) : fwd_k<T, S, false, false, false>(a, grid, queue, st);
 }
 
-template <int T, bool CUT, bool OIT>
+template <int T, int S, bool CUT, bool OIT>
 hipError_t bwd_k(const RasterArgs& a, int64_t grid, uint32_t* queue, hipStream_t st) {
-  return launch_items(raster_bwd_kernel<T, CUT, OIT, false>, raster_bwd_kernel<T, CUT, OIT, true>, a, grid, queue,
-                      kBwdThreads, st);
+  return launch_items(raster_bwd_kernel<T, S, CUT, OIT, false>, raster_bwd_kernel<T, S, CUT, OIT, true>, a, grid,
+                      queue, TileGeom<T>::kThreads, st);
 }
 
-template <int T>
-hipError_t bwd_t(const RasterArgs& a, int64_t grid, bool cut, bool oit, uint32_t* queue, hipStream_t st) {
-  if (oit) return bwd_k<T, false, true>(a, grid, queue, st);
-  if (cut) return bwd_k<T, true, false>(a, grid, queue, st);
-  return bwd_k<T, false, false>(a, grid, queue, st);
+template <int T, int S>
+hipError_t bwd_ts(const RasterArgs& a, int64_t grid, bool cut, bool oit, uint32_t* queue, hipStream_t st) {
+  if (oit) return bwd_k<T, S, false, true>(a, grid, queue, st);
+  if (cut) return bwd_k<T, S, true, false>(a, grid, queue, st);
+  return bwd_k<T, S, false, false>(a, grid, queue, st);
 }
 
-// Records the forward stages per batch: tile 8 (one wave, 64 threads) stages 64; tiles
+// Records staged per batch: tile 8 (one wave, 64 threads) stages 64; tiles
 // 16 and 32 take 64 (tile 16 only), 128 or 256 (the default).
 template <int T>
 hipError_t fwd_t(const RasterArgs& a, int64_t grid, int64_t tiles, int batch, bool count, bool cut, bool oit,
@@ -1746,6 +1623,17 @@ hipError_t fwd_t(const RasterArgs& a, int64_t grid, int64_t tiles, int batch, bo
   else
     raster_fwd_finalize<T, false><<<dim3(static_cast<unsigned>(tiles)), 256, 0, st>>>(a);
   return hipGetLastError();
+}
+
+template <int T>
+hipError_t bwd_t(const RasterArgs& a, int64_t grid, int batch, bool cut, bool oit, uint32_t* queue, hipStream_t st) {
+  if constexpr (T == 8) {
+    return bwd_ts<8, 64>(a, grid, cut, oit, queue, st);
+  } else {
+    if (batch == 128) return bwd_ts<T, 128>(a, grid, cut, oit, queue, st);
+    if (T == 16 && batch == 64) return bwd_ts<16, 64>(a, grid, cut, oit, queue, st);
+    return bwd_ts<T, 256>(a, grid, cut, oit, queue, st);
+  }
 }
 
 }  // namespace
@@ -1788,9 +1676,9 @@ hipError_t launch_raster_bwd(const Layout& L, void* ws, void* pairs, int64_t cap
   uint32_t* queue = (P->flags & WSR_FLAG_PERSISTENT) ? at<uint32_t>(ws, L.off_queue) + 1 : nullptr;
   const bool cut = P->alpha_cut > 0.f;
   switch (L.tile) {
-    case 8: return bwd_t<8>(a, grid, cut, oit, queue, st);
-    case 32: return bwd_t<32>(a, grid, cut, oit, queue, st);
-    default: return bwd_t<16>(a, grid, cut, oit, queue, st);
+    case 8: return bwd_t<8>(a, grid, P->batch, cut, oit, queue, st);
+    case 32: return bwd_t<32>(a, grid, P->batch, cut, oit, queue, st);
+    default: return bwd_t<16>(a, grid, P->batch, cut, oit, queue, st);
   }
 }
 
