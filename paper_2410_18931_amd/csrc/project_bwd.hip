@@ -378,27 +378,36 @@ __global__ __launch_bounds__(kBwdBlock) void project_bwd_kernel(BwdArgs a) {
 // Sum of each (view, Gaussian)'s per-tile partial 2D gradients: its pairs
 // occupy a contiguous range of Gaussian-major slots.  A light kernel of its
 // own, so the register-heavy chain below reads one 9-float gradient per
-// slot.  A lane sums the range of its own Gaussian when it is short; a long
-// range (a splat covering many tiles) is summed by the whole wave, lanes
-// striding through it, so the largest splats do not form a serial tail.
-// With OIT (DU) the same pass also sums each pair's dL/du through the
+// slot.  Bound by the reading of 36 bytes per pair.  Three neighbouring lanes
+// share a Gaussian, one float3 of the nine floats each, so that a load touches
+// a cache line or two per Gaussian for all 36 bytes instead of one for every
+// 12 (1 M Gaussians / 1080p, this kernel and the chain below: 273 us with a lane
+// per Gaussian, 261 now; sixteen views 1,455 and 1,406).  A long range (a splat covering many tiles) is summed by the whole
+// wave, lanes striding through it, so the largest splats do not form a serial
+// tail.  With OIT (DU) the same pass also sums each pair's dL/du through the
 // coverage term, which the raster stores in an array of its own.
 constexpr uint32_t kHeavySlots = 32;
+constexpr int kSumPerWave = kWave / 3;  // Gaussians of a wave
+constexpr int kSumWaves = 4;
+constexpr uint32_t kSumStep = 4;         // loads in flight per lane (6 and 8: 269 and 263 us instead of 261)
 
-__device__ __forceinline__ void add3(float* g, int o, const float3 v) {
-  g[o] += v.x;
-  g[o + 1] += v.y;
-  g[o + 2] += v.z;
+__device__ __forceinline__ void add3(float3& g, const float3 v) {
+  g.x += v.x;
+  g.y += v.y;
+  g.z += v.z;
 }
 
 template <bool DU>
-__global__ __launch_bounds__(256) void sum_pair_partials(const uint32_t* goff, const float3* part, const float* du,
-                                                         uint32_t capacity, int64_t slots, float* grad2d,
-                                                         float* out_grad2d, float* du2d) {
-  const int64_t k = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
-  const int lane = threadIdx.x % kWave;
+__global__ __launch_bounds__(kSumWaves* kWave) void sum_pair_partials(const uint32_t* goff, const float3* part,
+                                                                      const float* du, uint32_t capacity,
+                                                                      int64_t slots, float3* grad2d,
+                                                                      float3* out_grad2d, float* du2d) {
+  const int lane = threadIdx.x % kWave, third = lane % 3;
+  const int64_t first = (static_cast<int64_t>(blockIdx.x) * kSumWaves + threadIdx.x / kWave) * kSumPerWave;
+  const int64_t k = first + lane / 3;
+  const bool mine = lane < 3 * kSumPerWave && k < slots;
   uint32_t s0 = 0, s1 = 0;
-  if (k < slots) {
+  if (mine) {
     s0 = goff[k];
     s1 = goff[k + 1];
     s0 = s0 < capacity ? s0 : capacity;
@@ -406,76 +415,78 @@ __global__ __launch_bounds__(256) void sum_pair_partials(const uint32_t* goff, c
     if (s1 < s0) s1 = s0;
   }
   const bool heavy = s1 - s0 > kHeavySlots;
-  float g[9] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  float3 g = make_float3(0.f, 0.f, 0.f);
   float gu = 0.f;
   if (!heavy) {
-    // four slots per step keep twelve loads in flight per lane
+    const float3* p = part + 3 * static_cast<int64_t>(s0) + third;
     uint32_t j = s0;
-    for (; j + 4 <= s1; j += 4) {
-      const float3* p = part + 3 * static_cast<int64_t>(j);
-      const float3 x0 = p[0], x1 = p[1], x2 = p[2], y0 = p[3], y1 = p[4], y2 = p[5];
-      const float3 z0 = p[6], z1 = p[7], z2 = p[8], w0 = p[9], w1 = p[10], w2 = p[11];
-      add3(g, 0, x0); add3(g, 3, x1); add3(g, 6, x2);
-      add3(g, 0, y0); add3(g, 3, y1); add3(g, 6, y2);
-      add3(g, 0, z0); add3(g, 3, z1); add3(g, 6, z2);
-      add3(g, 0, w0); add3(g, 3, w1); add3(g, 6, w2);
-      if (DU) {
-        const float u0 = du[j], u1 = du[j + 1], u2 = du[j + 2], u3 = du[j + 3];
-        gu += u0;
-        gu += u1;
-        gu += u2;
-        gu += u3;
+    for (; j + kSumStep <= s1; j += kSumStep, p += 3 * kSumStep) {
+      float3 x[kSumStep];
+      float u[kSumStep];
+#pragma unroll
+      for (int q = 0; q < kSumStep; ++q) x[q] = p[3 * q];
+      if (DU)
+#pragma unroll
+        for (int q = 0; q < kSumStep; ++q) u[q] = du[j + q];
+#pragma unroll
+      for (int q = 0; q < kSumStep; ++q) add3(g, x[q]);
+      if (DU)
+#pragma unroll
+        for (int q = 0; q < kSumStep; ++q) gu += u[q];
+    }
+    // the rest, of which all loads are in flight at once
+    float3 x[kSumStep - 1];
+    float u[kSumStep - 1];
+#pragma unroll
+    for (int q = 0; q < kSumStep - 1; ++q) {
+      if (j + q < s1) {
+        x[q] = p[3 * q];
+        if (DU) u[q] = du[j + q];
       }
     }
-    for (; j + 2 <= s1; j += 2) {
-      const float3* p = part + 3 * static_cast<int64_t>(j);
-      const float3 x0 = p[0], x1 = p[1], x2 = p[2], y0 = p[3], y1 = p[4], y2 = p[5];
-      add3(g, 0, x0); add3(g, 3, x1); add3(g, 6, x2);
-      add3(g, 0, y0); add3(g, 3, y1); add3(g, 6, y2);
-      if (DU) {
-        const float u0 = du[j], u1 = du[j + 1];
-        gu += u0;
-        gu += u1;
+#pragma unroll
+    for (int q = 0; q < kSumStep - 1; ++q) {
+      if (j + q < s1) {
+        add3(g, x[q]);
+        if (DU) gu += u[q];
       }
-    }
-    if (j < s1) {
-      const float3* p = part + 3 * static_cast<int64_t>(j);
-      add3(g, 0, p[0]); add3(g, 3, p[1]); add3(g, 6, p[2]);
-      if (DU) gu += du[j];
     }
   }
   // the wave sums its heavy Gaussians one after another
-  uint64_t hmask = __ballot(heavy);
+  uint64_t hmask = __ballot(heavy && third == 0);
   while (hmask) {
     const int src = __ffsll(static_cast<long long>(hmask)) - 1;
     hmask &= hmask - 1;
     const uint32_t h0 = __shfl(s0, src, kWave), h1 = __shfl(s1, src, kWave);
-    float w[10] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    float3 w0 = make_float3(0.f, 0.f, 0.f), w1 = w0, w2 = w0;
+    float wu = 0.f;
     for (uint32_t j = h0 + lane; j < h1; j += kWave) {
       const float3* p = part + 3 * static_cast<int64_t>(j);
-      add3(w, 0, p[0]); add3(w, 3, p[1]); add3(w, 6, p[2]);
-      if (DU) w[9] += du[j];
+      add3(w0, p[0]);
+      add3(w1, p[1]);
+      add3(w2, p[2]);
+      if (DU) wu += du[j];
     }
-#pragma unroll
-    for (int q = 0; q < (DU ? 10 : 9); ++q) {
-      float x = w[q];
+    auto total = [](float x) {
 #pragma unroll
       for (int d = 32; d >= 1; d >>= 1) x += __shfl_xor(x, d, kWave);
-      if (lane == src) {
-        if (q < 9) g[q] = x;
-        else gu = x;
-      }
+      return x;
+    };
+    const float3 t0 = make_float3(total(w0.x), total(w0.y), total(w0.z));
+    const float3 t1 = make_float3(total(w1.x), total(w1.y), total(w1.z));
+    const float3 t2 = make_float3(total(w2.x), total(w2.y), total(w2.z));
+    if (lane == src) g = t0;
+    if (lane == src + 1) g = t1;
+    if (lane == src + 2) g = t2;
+    if (DU) {
+      const float t = total(wu);
+      if (lane == src) gu = t;
     }
   }
-  if (k >= slots) return;
-  float* d = grad2d + 9 * k;
-#pragma unroll
-  for (int q = 0; q < 9; ++q) d[q] = g[q];
-  if (out_grad2d) {
-#pragma unroll
-    for (int q = 0; q < 9; ++q) out_grad2d[9 * k + q] = g[q];
-  }
-  if (DU) du2d[k] = gu;
+  if (!mine) return;
+  grad2d[3 * k + third] = g;
+  if (out_grad2d) out_grad2d[3 * k + third] = g;
+  if (DU && third == 0) du2d[k] = gu;
 }
 
 // Final reduction of the global parameters: dL/dsigma, dL/dbeta from the
@@ -554,16 +565,18 @@ static hipError_t project_bwd_impl(const wsr_scene* sc, const wsr_params* P, con
     const PairView pv = pair_view(pairs, capacity);
     const int64_t slots = L.n * L.nv;
     const bool oit = (P->flags & WSR_FLAG_OIT) != 0;
-    const unsigned sblocks = static_cast<unsigned>((slots + 255) / 256);
+    constexpr int kPerBlock = kSumWaves * kSumPerWave;
+    const unsigned sblocks = static_cast<unsigned>((slots + kPerBlock - 1) / kPerBlock);
+    float3* grad2d = at<float3>(ws, L.off_grad2d);
+    float3* out2d = reinterpret_cast<float3*>(out_grad2d);
     if (oit)
-      sum_pair_partials<true><<<sblocks, 256, 0, st>>>(at<uint32_t>(ws, L.off_goff), pv.part, pv.du,
-                                                       static_cast<uint32_t>(capacity), slots,
-                                                       at<float>(ws, L.off_grad2d), out_grad2d,
-                                                       at<float>(ws, L.off_du2d));
+      sum_pair_partials<true><<<sblocks, kSumWaves * kWave, 0, st>>>(
+          at<uint32_t>(ws, L.off_goff), pv.part, pv.du, static_cast<uint32_t>(capacity), slots, grad2d, out2d,
+          at<float>(ws, L.off_du2d));
     else
-      sum_pair_partials<false><<<sblocks, 256, 0, st>>>(at<uint32_t>(ws, L.off_goff), pv.part, nullptr,
-                                                        static_cast<uint32_t>(capacity), slots,
-                                                        at<float>(ws, L.off_grad2d), out_grad2d, nullptr);
+      sum_pair_partials<false><<<sblocks, kSumWaves * kWave, 0, st>>>(
+          at<uint32_t>(ws, L.off_goff), pv.part, nullptr, static_cast<uint32_t>(capacity), slots, grad2d, out2d,
+          nullptr);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     BwdArgs a;
     a.means = sc->means;
