@@ -392,15 +392,18 @@ __global__ __launch_bounds__(kStripThreads, 4) void loss_strip_pass1(LossArgs a,
         syy = fmaf(g[q], hyy[r], syy);
         sxy = fmaf(g[q], hxy[r], sxy);
       }
-      const float a1 = 2.f * u * v + kC1;
-      const float a2 = 2.f * (sxy - u * v) + kC2;
-      const float b1 = u * u + v * v + kC1;
-      const float b2 = (sxx - u * u) + (syy - v * v) + kC2;
+      // the map and its derivatives, written out with the fused operations that
+      // the compiler forms in loss_pass1, so that both give the same bits
+      const float u2 = u + u, v2 = v + v;
+      const float a1 = fmaf(v, u2, kC1);
+      const float a2 = fmaf(2.f, fmaf(-v, u, sxy), kC2);
+      const float b1 = fmaf(v, v, u * u) + kC1;
+      const float b2 = (fmaf(-v, v, syy) + fmaf(-u, u, sxx)) + kC2;
       const float ib = 1.f / (b1 * b2);
       const float s = a1 * a2 * ib;
-      const float d_u = (2.f * v * a2 - 2.f * v * a1) * ib - s * (2.f * u / b1 - 2.f * u / b2);
+      const float d_u = fmaf(fmaf(v2, a2, -(v2 * a1)), ib, (u2 / b1 - u2 / b2) * -s);
       const float d_sxx = -s / b2;
-      const float d_sxy = 2.f * a1 * ib;
+      const float d_sxy = (a1 + a1) * ib;
       if (out_col) {
         const int64_t at = ch * a.total_pixels + w.pix_base + static_cast<int64_t>(oy) * w.width + w.x0;
         (a.dmap2 + at)[lane] = make_float2(d_u, d_sxx);
