@@ -1,5 +1,7 @@
 """GPU tests of the tile lists at the sizes where their kernels change form:
 the binning's block sizes and bands, and the per-tile depth sort."""
+import threading
+
 import numpy as np
 import pytest
 import torch
@@ -64,3 +66,35 @@ def test_sorted_list_order(length, depths):
     depth = sc["means"][2] + np.float32(4.0)
     np.testing.assert_array_equal(ent[:, 0], np.argsort(depth, kind="stable"))
     np.testing.assert_array_equal(ent[:, 1], ent[:, 0])
+
+
+def test_pair_counts_read_back_by_several_threads():
+    """Each thread reads the pair count of its own context on its own stream,
+    and gets that of the same scene binned alone."""
+    def count(n, repeat):
+        sc, cams, st = ws.make_scene("c1", n=n)
+        ctx = WSRContext(n, cams, st)
+        dev, g = scene_to_device(sc), globals_tensor(st)
+        torch.cuda.current_stream().synchronize()
+        got = set()
+        for _ in range(repeat):
+            ctx.project(dev, g)
+            ctx.bin(grow=True)
+            got.add(ctx.last_pairs)
+        return got
+
+    sizes = [500, 1000, 2000, 4000]
+    alone = [count(n, 1) for n in sizes]
+    found = [None] * len(sizes)
+
+    def work(k):
+        with torch.cuda.stream(torch.cuda.Stream()):
+            found[k] = count(sizes[k], 20)
+
+    log("case: pair counts from four threads")
+    threads = [threading.Thread(target=work, args=(k,)) for k in range(len(sizes))]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert found == alone
