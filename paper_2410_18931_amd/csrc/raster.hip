@@ -1142,13 +1142,6 @@ __device__ __forceinline__ void lds_barrier() {
   asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
-// LDS writes of this wave before, LDS reads of this wave after.
-__device__ __forceinline__ void lds_wave_fence() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // The per-tile sort.  A list is spread over equal steps of its depth range,
 // about as many buckets as entries (counted and placed with LDS atomics), and
 // every entry then finds its place by counting, in its bucket alone, the keys
@@ -1191,11 +1184,6 @@ struct SortShared {
   uint32_t lo, hi, work, wave[TH / kWave];
 };
 
-template <int TH>
-__device__ __forceinline__ void sort_sync() {
-  if constexpr (TH == kWave) lds_wave_fence(); else lds_barrier();
-}
-
 // Sorts keys[0, npow) in place (npow a power of two), between barriers.
 template <int TH>
 __device__ __forceinline__ void bitonic_keys(uint64_t* keys, int npow, int tid) {
@@ -1211,7 +1199,7 @@ __device__ __forceinline__ void bitonic_keys(uint64_t* keys, int npow, int tid) 
           keys[b] = x;
         }
       }
-      sort_sync<TH>();
+      lds_barrier();
     }
   }
 }
@@ -1219,7 +1207,7 @@ __device__ __forceinline__ void bitonic_keys(uint64_t* keys, int npow, int tid) 
 template <int CAP, int NB, int TH>
 __device__ __forceinline__ void sort_list(SortShared<CAP, NB, TH>& sh, const uint32_t* depths, uint2* ent, int len) {
   constexpr int R = CAP / TH;  // list positions per thread
-  const int tid = static_cast<int>(threadIdx.x) % TH, lane = tid % kWave;
+  const int tid = static_cast<int>(threadIdx.x), lane = tid % kWave;
   int npow = 64;
   while (npow < len) npow <<= 1;
   const int nb = min(npow, NB);
@@ -1228,7 +1216,7 @@ __device__ __forceinline__ void sort_list(SortShared<CAP, NB, TH>& sh, const uin
   for (int r = 0; r < R; ++r)
     if (r * TH < len) e[r] = ent[min(tid + r * TH, len - 1)];
   for (int k = tid; k < nb; k += TH) sh.hist[k] = 0u;
-  if (TH > kWave && tid == 0) {
+  if (tid == 0) {
     sh.lo = ~0u;
     sh.hi = 0u;
     sh.work = 0u;
@@ -1248,16 +1236,14 @@ __device__ __forceinline__ void sort_list(SortShared<CAP, NB, TH>& sh, const uin
     lo = min(lo, static_cast<uint32_t>(__shfl_xor(lo, d, kWave)));
     hi = max(hi, static_cast<uint32_t>(__shfl_xor(hi, d, kWave)));
   }
-  sort_sync<TH>();
-  if (TH > kWave) {
-    if (lane == 0) {
-      atomicMin(&sh.lo, lo);
-      atomicMax(&sh.hi, hi);
-    }
-    sort_sync<TH>();
-    lo = sh.lo;
-    hi = sh.hi;
+  lds_barrier();
+  if (lane == 0) {
+    atomicMin(&sh.lo, lo);
+    atomicMax(&sh.hi, hi);
   }
+  lds_barrier();
+  lo = sh.lo;
+  hi = sh.hi;
   const uint32_t span = hi - lo;
   // bucket of a depth: (depth - lo) nb / (span + 1), a little less
   const float step = 0.999f * 4294967296.f * static_cast<float>(nb) / (static_cast<float>(span) + 1.f);
@@ -1269,7 +1255,7 @@ __device__ __forceinline__ void sort_list(SortShared<CAP, NB, TH>& sh, const uin
       const uint32_t d = depth[r] - lo, b = mult ? __umulhi(d, mult) : d;
       place[r] = b << 16 | atomicAdd(&sh.hist[b], 1u);
     }
-  sort_sync<TH>();
+  lds_barrier();
   uint32_t work = 0u;  // comparisons
   {
     constexpr int P = (NB + TH - 1) / TH;
@@ -1289,16 +1275,14 @@ __device__ __forceinline__ void sort_list(SortShared<CAP, NB, TH>& sh, const uin
       const uint32_t o = __shfl_up(first, d, kWave);
       if (lane >= d) first += o;
     }
-    if (TH > kWave) {
-      if (lane == kWave - 1) {
-        sh.wave[tid / kWave] = first;
-        atomicAdd(&sh.work, work);
-      }
-      lds_barrier();
-#pragma unroll
-      for (int k = 0; k < TH / kWave; ++k) first += k < tid / kWave ? sh.wave[k] : 0u;
-      work = sh.work;
+    if (lane == kWave - 1) {
+      sh.wave[tid / kWave] = first;
+      atomicAdd(&sh.work, work);
     }
+    lds_barrier();
+#pragma unroll
+    for (int k = 0; k < TH / kWave; ++k) first += k < tid / kWave ? sh.wave[k] : 0u;
+    work = sh.work;
     first -= sum;
 #pragma unroll
     for (int k = 0; k < P; ++k)
@@ -1307,7 +1291,7 @@ __device__ __forceinline__ void sort_list(SortShared<CAP, NB, TH>& sh, const uin
         first += c[k];
       }
   }
-  sort_sync<TH>();
+  lds_barrier();
   auto key_of = [&](int r) { return static_cast<uint64_t>(depth[r]) << 32 | static_cast<uint32_t>(tid + r * TH); };
 #pragma unroll
   for (int r = 0; r < R; ++r)
@@ -1317,7 +1301,7 @@ __device__ __forceinline__ void sort_list(SortShared<CAP, NB, TH>& sh, const uin
       place[r] = h;
     }
   if (work <= kSortCrowd * static_cast<uint32_t>(len)) {
-    sort_sync<TH>();
+    lds_barrier();
 #pragma unroll
     for (int r = 0; r < R; ++r)
       if (tid + r * TH < len) {
@@ -1331,25 +1315,24 @@ __device__ __forceinline__ void sort_list(SortShared<CAP, NB, TH>& sh, const uin
         place[r] = pos;
       }
     // through LDS, so that the list is stored in order
-    sort_sync<TH>();
+    lds_barrier();
     uint2* sorted = reinterpret_cast<uint2*>(sh.keys);
 #pragma unroll
     for (int r = 0; r < R; ++r)
       if (tid + r * TH < len) sorted[place[r]] = e[r];
-    sort_sync<TH>();
+    lds_barrier();
 #pragma unroll
     for (int r = 0; r < R; ++r)
       if (tid + r * TH < len) ent[tid + r * TH] = sorted[tid + r * TH];
   } else {
     for (int k = len + tid; k < npow; k += TH) sh.keys[k] = ~0ull;  // sorts last
-    sort_sync<TH>();
+    lds_barrier();
     bitonic_keys<TH>(sh.keys, npow, tid);
     // the position in a key leads back to its entry
 #pragma unroll
     for (int r = 0; r < R; ++r)
       if (tid + r * TH < len) e[r] = ent[static_cast<uint32_t>(sh.keys[tid + r * TH])];
-    if (TH > kWave) __syncthreads();  // every old entry has been read
-    else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();  // every old entry has been read
 #pragma unroll
     for (int r = 0; r < R; ++r)
       if (tid + r * TH < len) ent[tid + r * TH] = e[r];
@@ -1359,7 +1342,7 @@ __device__ __forceinline__ void sort_list(SortShared<CAP, NB, TH>& sh, const uin
 // The lists of up to kSortSmall entries, i.e. the tiles of one work item, one
 // workgroup each, longest first; the others' tiles go to the queue.
 constexpr int kSortThreads = 256;
-__global__ __launch_bounds__(kSortThreads, 8) void sort_short_kernel(const DevCamera* cams, int32_t nv,
+__global__ __launch_bounds__(kSortThreads, 7) void sort_short_kernel(const DevCamera* cams, int32_t nv,
                                                                      const uint32_t* depths, int64_t n,
                                                                      const uint4* tile_order, uint2* ent,
                                                                      SortQueue queue, DevFlags* flags) {
