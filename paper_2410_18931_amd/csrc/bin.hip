@@ -2,11 +2,11 @@
 // Eq. 7 is a commutative sum (Sec. 4.2), so only membership matters; this is
 // the step that replaces the per-tile depth sort of 3DGS (Sec. 4.1).
 //
-// A counting sort by tile built from LDS histograms, with no global atomics:
+// A counting sort by tile, with no global atomics:
 //   1. bin_pass<count>: block (b, z, v) takes Gaussians [b*chunk, ...) of
-//      view v and counts their (tile, Gaussian) pairs into an LDS histogram
-//      of the tile rows of band z, written contiguously as row b of the
-//      block-major count matrix M[v][b][tile].
+//      view v and counts their (tile, Gaussian) pairs in the tile rows of
+//      band z, as prefix sums of the rectangles' corners in LDS, written
+//      contiguously as row b of the block-major count matrix M[v][b][tile].
 //   2. column_scan_wide: each tile's column of M becomes exclusive prefixes
 //      over the blocks, and the tile's total; tile_scan_single scans the
 //      totals into the start of every tile's list (tile_start).
@@ -25,8 +25,8 @@
 // tile of its rectangle in row-major order.  Its first slot, goff, is the
 // exclusive scan of the rectangle sizes in (view, Gaussian) order, formed by
 // the same passes: the counting pass's first band also sums each block's
-// rectangle sizes, scan_parts scans those block sums, and the scatter pass's
-// first band writes goff.  The raster work items that split long tile lists
+// rectangle sizes, scan_parts (in tile_scan_single's second workgroup) scans
+// those block sums, and the scatter pass's first band writes goff.  The raster work items that split long tile lists
 // come from tile_scan_single.
 #include "wsr_internal.h"
 
