@@ -71,8 +71,9 @@ hipError_t read_flags(const void* ws, hipStream_t st, DevFlags* f) {
   make_layout(0, &probe, 1, 16, &L, nullptr);
   hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
   static thread_local PinnedFlags pinned;
-  DevFlags* to = hipStreamIsCapturing(st, &capture) == hipSuccess && capture == hipStreamCaptureStatusNone
-                     ? pinned.get() : nullptr;
+  DevFlags* to = nullptr;
+  if (hipStreamIsCapturing(st, &capture) != hipSuccess) (void)hipGetLastError();
+  else if (capture == hipStreamCaptureStatusNone) to = pinned.get();
   hipError_t e = hipMemcpyAsync(to ? to : f, at<DevFlags>(ws, L.off_flags), sizeof(*f), hipMemcpyDeviceToHost, st);
   if (e == hipSuccess) e = hipStreamSynchronize(st);
   if (e == hipSuccess && to) *f = *to;
