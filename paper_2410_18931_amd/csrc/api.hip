@@ -5,6 +5,7 @@
 #include <cstring>
 
 #include "adam.h"
+#include "status_slots.h"
 #include "wsr_internal.h"
 
 namespace wsr {
@@ -33,28 +34,35 @@ int32_t to_status(hipError_t e) { return e == hipSuccess ? WSR_OK : WSR_ERR_HIP;
 constexpr int kBinChunkMin = 256, kBinChunkMax = 2048;
 constexpr int64_t kBinSmall = 1 << 20;
 
+// Page-locked memory for the slots of all threads (see status_slots.h).
+void* alloc_status_page(size_t bytes) {
+  // allocating must not disturb another thread's stream capture
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  const bool swapped = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+  void* p = nullptr;
+  if (hipHostMalloc(&p, bytes, hipHostMallocPortable) != hipSuccess) {
+    p = nullptr;
+    (void)hipGetLastError();
+  }
+  if (swapped) (void)hipThreadExchangeStreamCaptureMode(&mode);
+  return p;
+}
+
 // The calling thread's page-locked copy of the status words: a device-to-host
 // copy into pageable memory is staged by the runtime and costs the caller about
 // 20 us more (a pass over 4,096 Gaussians with its read-back: 92 -> 76 us; 30 k
-// Gaussians in three views with loss and update: 222 -> 197 us).  64 bytes per
-// thread that reads status words, given back when the thread ends.
+// Gaussians in three views with loss and update: 222 -> 197 us).
 struct PinnedFlags {
+  static_assert(sizeof(DevFlags) <= StatusSlots::kSlotBytes, "slot size");
   DevFlags* p = nullptr;
   bool tried = false;
   ~PinnedFlags() {
-    if (p) (void)hipHostFree(p);
+    if (p) StatusSlots::process().give(p);
   }
   DevFlags* get() {
     if (!tried) {
       tried = true;
-      // allocating must not disturb another thread's stream capture
-      hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
-      const bool swapped = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
-      if (hipHostMalloc(reinterpret_cast<void**>(&p), sizeof(DevFlags), hipHostMallocPortable) != hipSuccess) {
-        p = nullptr;
-        (void)hipGetLastError();
-      }
-      if (swapped) (void)hipThreadExchangeStreamCaptureMode(&mode);
+      p = static_cast<DevFlags*>(StatusSlots::process().take(alloc_status_page));
     }
     return p;
   }
@@ -77,6 +85,7 @@ hipError_t read_flags(const void* ws, hipStream_t st, DevFlags* f) {
   hipError_t e = hipMemcpyAsync(to ? to : f, at<DevFlags>(ws, L.off_flags), sizeof(*f), hipMemcpyDeviceToHost, st);
   if (e == hipSuccess) e = hipStreamSynchronize(st);
   if (e == hipSuccess && to) *f = *to;
+  if (e != hipSuccess && to) pinned.p = nullptr;  // a copy may still be under way: the slot is not used again
   return e;
 }
 
