@@ -248,7 +248,10 @@ __device__ __forceinline__ void tile_setup(const RasterArgs& a, uint32_t item, T
   // laid out: first the full items, tile by tile, then the tiles' last items
   // in tile_order
   const uint32_t nfull = a.items[a.total_tiles] - static_cast<uint32_t>(a.total_tiles);
-  uint32_t s0, e0;  // the tile's list, capped at the capacity
+  // the tile's list, capped at this call's capacity (the descriptors hold ends
+  // capped at the binning's)
+  const uint32_t cap = static_cast<uint32_t>(a.capacity);
+  uint32_t s0, e0;
   if (item < nfull) {
     // largest tile t with items[t] - t <= item (nondecreasing in t)
     int64_t lo = 0, hi = a.total_tiles - 1;
@@ -259,10 +262,8 @@ __device__ __forceinline__ void tile_setup(const RasterArgs& a, uint32_t item, T
     c.tile = lo;
     c.k = item - (a.items[lo] - static_cast<uint32_t>(lo));
     c.nk = a.items[lo + 1] - a.items[lo];
-    const uint64_t cap = static_cast<uint64_t>(a.capacity);
-    s0 = static_cast<uint32_t>(min(static_cast<uint64_t>(a.tile_start[lo]), cap));
-    e0 = static_cast<uint32_t>(min(static_cast<uint64_t>(a.tile_start[lo + 1]), cap));
-    if (e0 < s0) e0 = s0;
+    s0 = a.tile_start[lo];
+    e0 = a.tile_start[lo + 1];
   } else {
     const uint4 d = a.tile_order[item - nfull];
     c.tile = d.x;
@@ -271,6 +272,8 @@ __device__ __forceinline__ void tile_setup(const RasterArgs& a, uint32_t item, T
     s0 = d.y;
     e0 = d.z;
   }
+  s0 = min(s0, cap);
+  e0 = max(min(e0, cap), s0);
   const int tile = static_cast<int>(c.tile);
   c.v = find_view(a.cams, a.nv, tile);
   cam = &a.cams[c.v];
@@ -1344,13 +1347,13 @@ __device__ __forceinline__ void sort_list(SortShared<CAP, NB, TH>& sh, const uin
 constexpr int kSortThreads = 256;
 __global__ __launch_bounds__(kSortThreads, 7) void sort_short_kernel(const DevCamera* cams, int32_t nv,
                                                                      const uint32_t* depths, int64_t n,
-                                                                     const uint4* tile_order, uint2* ent,
-                                                                     SortQueue queue, DevFlags* flags) {
+                                                                     const uint4* tile_order, uint32_t capacity,
+                                                                     uint2* ent, SortQueue queue, DevFlags* flags) {
   __shared__ SortShared<kSortSmall, 1024, kSortThreads> sh;
   // entries move: culling masks stored for the old positions no longer apply
   if (blockIdx.x == 0 && threadIdx.x == 0) flags->cull_masks = 0u;
   const uint4 d = tile_order[blockIdx.x];  // (tile, list first, list end, work items)
-  const uint32_t len = d.z - d.y;
+  const uint32_t first = min(d.y, capacity), len = min(d.z, capacity) - first;
   if (len > static_cast<uint32_t>(kSortSmall)) {
     if (threadIdx.x == 0) {
       if (len > static_cast<uint32_t>(kSortMax)) flags->sort_overflow = 1u;
@@ -1359,7 +1362,7 @@ __global__ __launch_bounds__(kSortThreads, 7) void sort_short_kernel(const DevCa
     }
   } else if (len > 1u) {
     const int v = find_view(cams, nv, static_cast<int>(d.x));
-    sort_list(sh, depths + static_cast<int64_t>(v) * n, ent + d.y, static_cast<int>(len));
+    sort_list(sh, depths + static_cast<int64_t>(v) * n, ent + first, static_cast<int>(len));
   }
 }
 
@@ -1705,7 +1708,7 @@ hipError_t launch_sort_tiles(const Layout& L, void* ws, void* pairs, int64_t cap
   sort_depths_kernel<<<static_cast<unsigned>(slots / 256 + 1), 256, 0, st>>>(at<DevSplat>(ws, L.off_rec), depths,
                                                                              slots, queue.head);
   sort_short_kernel<<<static_cast<unsigned>(L.total_tiles), kSortThreads, 0, st>>>(
-      cams, L.nv, depths, L.n, at<uint4>(ws, L.off_torder), pv.ent, queue, flags);
+      cams, L.nv, depths, L.n, at<uint4>(ws, L.off_torder), static_cast<uint32_t>(capacity), pv.ent, queue, flags);
   // as many workgroups as run at once, and no more than there can be lists
   if (capacity > kSortSmall)
     sort_long_kernel<kSortMid><<<static_cast<unsigned>(std::min<int64_t>({512, L.total_tiles, capacity / kSortSmall})),
