@@ -26,14 +26,14 @@
 // exclusive scan of the rectangle sizes in (view, Gaussian) order, formed by
 // the same passes: the counting pass's first band also sums each block's
 // rectangle sizes, scan_parts (in tile_scan_single's second workgroup) scans
-// those block sums, and the scatter pass's first band writes goff.  The raster work items that split long tile lists
-// come from tile_scan_single.
+// those block sums, and the scatter pass's first band writes goff.  The raster
+// work items that split long tile lists come from tile_scan_single.
+#include "plan.h"
 #include "wsr_internal.h"
 
 namespace wsr {
 namespace {
 
-constexpr int kBinThreads = 256;
 constexpr int kBinWaves = kBinThreads / kWave;
 
 // Inclusive sum over the lanes of a wave, in registers (DPP row shifts, then
@@ -68,7 +68,6 @@ struct BinArgs {
   int32_t chunk;               // Gaussians per block, a multiple of kBinThreads
   uint32_t* parts;             // per (view, block): sum of the rectangle sizes, then its exclusive scan
   uint32_t* goff;              // Gaussian-major first slot of every (view, Gaussian)
-  int bands;                 // bands of tile rows per view
 };
 
 // One Gaussian's tile rectangle, whole and cut to a band of tile rows.
@@ -201,8 +200,7 @@ __global__ __launch_bounds__(kBinThreads) void bin_pass(BinArgs a) {
   // that lie side by side are written through one L2 (the stage at 1 M
   // Gaussians / 1080p 175 -> 166 us, 16 views 1,398 -> 1,273 us; with a part of
   // the bands per XCD instead, whose loads differ, 203 and 1,475 us).
-  const uint32_t per = (a.nblk + 7) / 8, k = blockIdx.x / 8;
-  const int b = blockIdx.x % 8 * per + k % per, z = k / per % a.bands, v = k / per / a.bands;
+  const int b = blockIdx.x % 8 * (gridDim.x / 8) + blockIdx.x / 8, z = blockIdx.y, v = blockIdx.z;
   if (b >= a.nblk) return;
   const DevCamera& cam = a.cams[v];
   const int tiles_x = cam.tiles_x;
@@ -556,8 +554,8 @@ hipError_t launch_bin(const Layout& L, void* ws, void* pairs, int64_t capacity, 
   if (a.rows_per_chunk < 1) a.rows_per_chunk = 1;
   const int nchunks = (L.max_tiles_y + a.rows_per_chunk - 1) / a.rows_per_chunk;
   const size_t lds = static_cast<size_t>(a.rows_per_chunk) * L.max_tiles_x * sizeof(uint32_t);
-  a.bands = nchunks;
-  const unsigned grid = static_cast<unsigned>(static_cast<int64_t>((L.nblk + 7) / 8 * 8) * nchunks * L.nv);
+  const GridShape gs = bin_grid(L.nblk, nchunks, L.nv);
+  const dim3 grid(gs.x, gs.y, gs.z);
 
   hipError_t e;
   bin_pass<false><<<grid, kBinThreads, lds, st>>>(a);

@@ -1,0 +1,39 @@
+"""csrc/plan.h built with the host compiler, for tests of its rules."""
+import ctypes as C
+import functools
+import os
+import subprocess
+import tempfile
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+WRAPPERS = r"""
+#include "plan.h"
+extern "C" {
+void bin_grid(int64_t nblk, int64_t bands, int64_t nv, int64_t* g) {
+  const wsr::GridShape s = wsr::bin_grid(nblk, bands, nv);
+  g[0] = s.x; g[1] = s.y; g[2] = s.z;
+}
+int64_t bin_threads() { return wsr::kBinThreads; }
+}
+"""
+
+
+@functools.lru_cache(None)
+def load():
+    out = tempfile.mkdtemp(prefix="wsr_plan_")
+    src, lib = os.path.join(out, "plan.cpp"), os.path.join(out, "libplan.so")
+    with open(src, "w") as f:
+        f.write(WRAPPERS)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-fPIC", "-shared", "-I",
+                    os.path.join(ROOT, "paper_2410_18931_amd", "csrc"), src, "-o", lib], check=True)
+    plan = C.CDLL(lib)
+    plan.bin_threads.restype = C.c_int64
+    plan.bin_grid.argtypes = [C.c_int64, C.c_int64, C.c_int64, C.c_void_p]
+    return plan
+
+
+def grid(name, *args):
+    g = (C.c_int64 * 3)()
+    getattr(load(), name)(*args, g)
+    return tuple(g)

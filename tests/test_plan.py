@@ -1,0 +1,19 @@
+"""CPU tests of the launch shapes (csrc/plan.h) over the range of the sizes."""
+import pytest
+
+from tests import plan_lib
+
+LIMIT = 1 << 32  # workgroups times threads of a dimension stay below this
+
+
+@pytest.mark.parametrize("nblk,bands,nv", [
+    (1, 1, 1), (8, 6, 1), (489, 6, 16), (2051, 4096, 2), (1954, 4096, 256), (1 << 21, 6, 1), (40_000, 6, 256)])
+def test_binning_grid(nblk, bands, nv):
+    """Every (block, band, view) has a workgroup of its own, at sizes where one
+    dimension would not hold them all too (a wide and a tall view: 4,096 bands)."""
+    x, y, z = plan_lib.grid("bin_grid", nblk, bands, nv)
+    assert x % 8 == 0 and nblk <= x < nblk + 8 and y == bands and z == nv
+    assert x * plan_lib.load().bin_threads() < LIMIT and y <= 65535 and z <= 65535
+    # block (i % 8) x / 8 + i / 8 of workgroup i: each block once
+    if x <= 4096:
+        assert sorted(i % 8 * (x // 8) + i // 8 for i in range(x)) == list(range(x))
