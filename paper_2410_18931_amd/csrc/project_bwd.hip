@@ -11,6 +11,7 @@
 // partials (deterministic, no float atomics).
 #include "adam.h"
 #include "geom.h"
+#include "plan.h"
 #include "sh_basis.h"
 #include "wsr_internal.h"
 
@@ -387,8 +388,6 @@ __global__ __launch_bounds__(kBwdBlock) void project_bwd_kernel(BwdArgs a) {
 // tail.  With OIT (DU) the same pass also sums each pair's dL/du through the
 // coverage term, which the raster stores in an array of its own.
 constexpr uint32_t kHeavySlots = 32;
-constexpr int kSumPerWave = kWave / 3;  // Gaussians of a wave
-constexpr int kSumWaves = 4;
 constexpr uint32_t kSumStep = 4;         // loads in flight per lane (6 and 8: 269 and 263 us instead of 261)
 
 __device__ __forceinline__ void add3(float3& g, const float3 v) {
@@ -403,7 +402,8 @@ __global__ __launch_bounds__(kSumWaves* kWave) void sum_pair_partials(const uint
                                                                       int64_t slots, float3* grad2d,
                                                                       float3* out_grad2d, float* du2d) {
   const int lane = threadIdx.x % kWave, third = lane % 3;
-  const int64_t first = (static_cast<int64_t>(blockIdx.x) * kSumWaves + threadIdx.x / kWave) * kSumPerWave;
+  const int64_t block = static_cast<int64_t>(blockIdx.y) * gridDim.x + blockIdx.x;
+  const int64_t first = (block * kSumWaves + threadIdx.x / kWave) * kSumPerWave;
   const int64_t k = first + lane / 3;
   const bool mine = lane < 3 * kSumPerWave && k < slots;
   uint32_t s0 = 0, s1 = 0;
@@ -565,16 +565,16 @@ static hipError_t project_bwd_impl(const wsr_scene* sc, const wsr_params* P, con
     const PairView pv = pair_view(pairs, capacity);
     const int64_t slots = L.n * L.nv;
     const bool oit = (P->flags & WSR_FLAG_OIT) != 0;
-    constexpr int kPerBlock = kSumWaves * kSumPerWave;
-    const unsigned sblocks = static_cast<unsigned>((slots + kPerBlock - 1) / kPerBlock);
+    const GridShape gs = sum_grid(slots);
+    const dim3 sgrid(gs.x, gs.y, gs.z);
     float3* grad2d = at<float3>(ws, L.off_grad2d);
     float3* out2d = reinterpret_cast<float3*>(out_grad2d);
     if (oit)
-      sum_pair_partials<true><<<sblocks, kSumWaves * kWave, 0, st>>>(
+      sum_pair_partials<true><<<sgrid, kSumWaves * kWave, 0, st>>>(
           at<uint32_t>(ws, L.off_goff), pv.part, pv.du, static_cast<uint32_t>(capacity), slots, grad2d, out2d,
           at<float>(ws, L.off_du2d));
     else
-      sum_pair_partials<false><<<sblocks, kSumWaves * kWave, 0, st>>>(
+      sum_pair_partials<false><<<sgrid, kSumWaves * kWave, 0, st>>>(
           at<uint32_t>(ws, L.off_goff), pv.part, nullptr, static_cast<uint32_t>(capacity), slots, grad2d, out2d,
           nullptr);
     if ((e = hipGetLastError()) != hipSuccess) return e;

@@ -14,7 +14,13 @@ void bin_grid(int64_t nblk, int64_t bands, int64_t nv, int64_t* g) {
   const wsr::GridShape s = wsr::bin_grid(nblk, bands, nv);
   g[0] = s.x; g[1] = s.y; g[2] = s.z;
 }
+void sum_grid(int64_t slots, int64_t* g) {
+  const wsr::GridShape s = wsr::sum_grid(slots);
+  g[0] = s.x; g[1] = s.y; g[2] = s.z;
+}
 int64_t bin_threads() { return wsr::kBinThreads; }
+int64_t sum_waves() { return wsr::kSumWaves; }
+int64_t sum_per_wave() { return wsr::kSumPerWave; }
 }
 """
 
@@ -28,8 +34,10 @@ def load():
     subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-fPIC", "-shared", "-I",
                     os.path.join(ROOT, "paper_2410_18931_amd", "csrc"), src, "-o", lib], check=True)
     plan = C.CDLL(lib)
-    plan.bin_threads.restype = C.c_int64
+    for name in ("bin_threads", "sum_waves", "sum_per_wave"):
+        getattr(plan, name).restype = C.c_int64
     plan.bin_grid.argtypes = [C.c_int64, C.c_int64, C.c_int64, C.c_void_p]
+    plan.sum_grid.argtypes = [C.c_int64, C.c_void_p]
     return plan
 
 

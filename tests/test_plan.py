@@ -17,3 +17,18 @@ def test_binning_grid(nblk, bands, nv):
     # block (i % 8) x / 8 + i / 8 of workgroup i: each block once
     if x <= 4096:
         assert sorted(i % 8 * (x // 8) + i // 8 for i in range(x)) == list(range(x))
+
+
+@pytest.mark.parametrize("slots", [1, 83, 84, 85, 5000, 16_000_000, 84 << 22, (84 << 22) + 1, 1_409_286_144,
+                                   1_409_286_145, 2_200_000_000, LIMIT - 1])
+def test_pair_sum_grid(slots):
+    """The (view, Gaussian)s of all rows of workgroups cover every slot, with
+    less than one row too many, up to the largest slot count."""
+    plan = plan_lib.load()
+    x, y, z = plan_lib.grid("sum_grid", slots)
+    per = plan.sum_waves() * plan.sum_per_wave()
+    assert per == 84 and z == 1
+    assert x * y * per >= slots and x * (y - 1) * per < slots
+    assert x * plan.sum_waves() * 64 < LIMIT and y <= 65535
+    if slots <= per << 22:
+        assert (x, y) == ((slots + per - 1) // per, 1)
