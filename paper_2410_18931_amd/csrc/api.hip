@@ -1,10 +1,10 @@
 // C-ABI entry points of the WSR library (declared in include/wsr.h): argument
 // checks, workspace layout, and the launch sequence of each step.
-#include <algorithm>
 #include <cmath>
 #include <cstring>
 
 #include "adam.h"
+#include "plan.h"
 #include "status_slots.h"
 #include "wsr_internal.h"
 
@@ -21,18 +21,6 @@ bool valid_tile(int32_t t) { return t == 8 || t == 16 || t == 32; }
 int32_t to_status(hipError_t e) { return e == hipSuccess ? WSR_OK : WSR_ERR_HIP; }
 
 }  // namespace
-
-// Gaussians per binning block: the fewest, 256 to 2,048, whose count matrix
-// (blocks x tiles) stays within kBinSmall entries.  With few Gaussians or tiles
-// a block's serial expansion is the whole pass and wants to be short (4,096
-// Gaussians at 128 x 128: 43 us of binning passes in blocks of 2,048, 10 us in
-// blocks of 256); with many the matrix's traffic grows with the blocks (1 M
-// Gaussians at 1080p: the stage takes 175 us in blocks of 2,048, 206 us in
-// blocks of 1,024, 177 us in blocks of 4,096).  200 k Gaussians at 1280 x 720
-// and 300 k at 1001 x 747 take 49 and 55 us with the line here, 54 and 56 us
-// with it at half and 53 and 67 us at twice as many entries.
-constexpr int kBinChunkMin = 256, kBinChunkMax = 2048;
-constexpr int64_t kBinSmall = 1 << 20;
 
 // Page-locked memory for the slots of all threads (see status_slots.h).
 void* alloc_status_page(size_t bytes) {
@@ -89,8 +77,6 @@ hipError_t read_flags(const void* ws, hipStream_t st, DevFlags* f) {
   return e;
 }
 
-int64_t blocks_of(int64_t n, int64_t chunk) { return n > 0 ? (n + chunk - 1) / chunk : 1; }
-
 bool make_layout(int64_t n, const wsr_camera* cams, int32_t nv, int32_t tile, Layout* L, DevCamera* dc) {
   if (n < 0 || n > 0xffffffffLL || !cams || nv < 1 || nv > WSR_MAX_VIEWS || !valid_tile(tile)) return false;
   *L = Layout();
@@ -105,12 +91,9 @@ bool make_layout(int64_t n, const wsr_camera* cams, int32_t nv, int32_t tile, La
     tiles += static_cast<int64_t>((c.width + tile - 1) / tile) * ((c.height + tile - 1) / tile);
   }
   if (tiles > 0x7fffffffLL) return false;
-  L->bin_chunk = kBinChunkMin;
-  while (L->bin_chunk < kBinChunkMax && blocks_of(n, L->bin_chunk) * tiles > kBinSmall) L->bin_chunk *= 2;
-  L->nblk = static_cast<int32_t>(blocks_of(n, L->bin_chunk));
-  // the largest matrix of any chunk for up to n Gaussians, so that a workspace
-  // never holds fewer Gaussians than it was sized for
-  const int64_t hist_room = std::max(blocks_of(n, kBinChunkMax) * tiles, std::min(blocks_of(n, kBinChunkMin) * tiles, kBinSmall));
+  L->bin_chunk = bin_chunk(n, tiles);
+  L->nblk = static_cast<int32_t>(bin_blocks(n, L->bin_chunk));
+  const int64_t hist_room = bin_matrix_room(n, tiles);
   int64_t hist = 0;
   tiles = 0;
   for (int v = 0; v < nv; ++v) {
@@ -150,7 +133,7 @@ bool make_layout(int64_t n, const wsr_camera* cams, int32_t nv, int32_t tile, La
   L->off_rec = off;      off = align256(off + sizeof(DevSplat) * slots);
   L->off_rect = off;     off = align256(off + sizeof(uint2) * slots);
   L->off_hist = off;     off = align256(off + sizeof(uint32_t) * (hist_room + 1));
-  L->off_scan = off;     off = align256(off + sizeof(uint32_t) * nv * blocks_of(n, kBinChunkMin));
+  L->off_scan = off;     off = align256(off + sizeof(uint32_t) * nv * bin_blocks(n, kBinChunkMin));
   L->off_goff = off;     off = align256(off + sizeof(uint32_t) * (slots + 1));
   L->off_grad2d = off;   off = align256(off + sizeof(float) * 9 * slots);
   L->off_tstart = off;   off = align256(off + sizeof(uint32_t) * (tiles + 1));

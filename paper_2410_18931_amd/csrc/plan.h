@@ -1,6 +1,7 @@
 // Launch shapes that follow from the caller's sizes alone.  Plain C++, so that
 // the rules can be checked over their whole range without a GPU.
 #pragma once
+#include <algorithm>
 #include <cstdint>
 
 namespace wsr {
@@ -10,6 +11,39 @@ namespace wsr {
 struct GridShape {
   uint32_t x, y, z;
 };
+
+// Gaussians per binning block: the fewest, 256 to 2,048, with at most kBinBlocks
+// blocks a view and a count matrix (blocks x tiles) of at most kBinSmall
+// entries.  With few Gaussians or tiles a block's serial expansion is the whole
+// pass and wants to be short (4,096 Gaussians at 128 x 128: 43 us of binning
+// passes in blocks of 2,048, 10 us in blocks of 256); with many the matrix's
+// traffic grows with the blocks (1 M Gaussians at 1080p: the stage takes 175 us
+// in blocks of 2,048, 206 us in blocks of 1,024, 177 us in blocks of 4,096).
+// 200 k Gaussians at 1280 x 720 and 300 k at 1001 x 747 take 49 and 55 us with
+// the line here, 54 and 56 us with it at half and 53 and 67 us at twice as many
+// entries.  A column of the matrix is a serial chain over the blocks, which a
+// small image has nothing to hide behind: the stage for 500 k Gaussians at
+// 128 x 128 takes 50, 52 and 67 us with at most 256, 512 and 1,024 blocks
+// (101 without a limit, 63 in blocks of 2,048 throughout), for 300 k in twelve
+// views of 200 x 133 166, 177 and 211 us.
+constexpr int32_t kBinChunkMin = 256, kBinChunkMax = 2048;
+constexpr int64_t kBinSmall = 1 << 20, kBinBlocks = 256;
+
+inline int64_t bin_blocks(int64_t n, int64_t chunk) { return n > 0 ? (n + chunk - 1) / chunk : 1; }
+
+inline int32_t bin_chunk(int64_t n, int64_t tiles) {
+  int32_t chunk = kBinChunkMin;
+  while (chunk < kBinChunkMax && (bin_blocks(n, chunk) > kBinBlocks || bin_blocks(n, chunk) * tiles > kBinSmall))
+    chunk *= 2;
+  return chunk;
+}
+
+// Entries to hold the count matrix of every Gaussian count up to n: a workspace
+// never holds fewer Gaussians than it was sized for.
+inline int64_t bin_matrix_room(int64_t n, int64_t tiles) {
+  const int64_t most = bin_blocks(n, kBinChunkMin) * tiles;
+  return std::max(bin_blocks(n, kBinChunkMax) * tiles, std::min(most, kBinSmall));
+}
 
 // Binning passes: x the blocks of a view, rounded up to whole eighths (one for
 // each XCD), y the bands, z the views.  Workgroups start with x fastest, so

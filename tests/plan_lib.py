@@ -18,6 +18,9 @@ void sum_grid(int64_t slots, int64_t* g) {
   const wsr::GridShape s = wsr::sum_grid(slots);
   g[0] = s.x; g[1] = s.y; g[2] = s.z;
 }
+int64_t bin_blocks(int64_t n, int64_t chunk) { return wsr::bin_blocks(n, chunk); }
+int64_t bin_chunk(int64_t n, int64_t tiles) { return wsr::bin_chunk(n, tiles); }
+int64_t bin_matrix_room(int64_t n, int64_t tiles) { return wsr::bin_matrix_room(n, tiles); }
 int64_t bin_threads() { return wsr::kBinThreads; }
 int64_t sum_waves() { return wsr::kSumWaves; }
 int64_t sum_per_wave() { return wsr::kSumPerWave; }
@@ -34,6 +37,9 @@ def load():
     subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-fPIC", "-shared", "-I",
                     os.path.join(ROOT, "paper_2410_18931_amd", "csrc"), src, "-o", lib], check=True)
     plan = C.CDLL(lib)
+    for name in ("bin_blocks", "bin_chunk", "bin_matrix_room"):
+        getattr(plan, name).argtypes = [C.c_int64, C.c_int64]
+        getattr(plan, name).restype = C.c_int64
     for name in ("bin_threads", "sum_waves", "sum_per_wave"):
         getattr(plan, name).restype = C.c_int64
     plan.bin_grid.argtypes = [C.c_int64, C.c_int64, C.c_int64, C.c_void_p]

@@ -32,3 +32,24 @@ def test_pair_sum_grid(slots):
     assert x * plan.sum_waves() * 64 < LIMIT and y <= 65535
     if slots <= per << 22:
         assert (x, y) == ((slots + per - 1) // per, 1)
+
+
+@pytest.mark.parametrize("tiles", [1, 64, 104, 920, 3600, 8160, 60_000, 129_600, 16_777_216])
+def test_binning_blocks(tiles):
+    """Blocks grow before their number, the length of a column of the count
+    matrix, passes 256 or the matrix 2^20 entries, and no workspace has less
+    room than a smaller Gaussian count needs."""
+    plan = plan_lib.load()
+    room = 0
+    for n in [0, 1, 255, 256, 257, 4096, 30_011, 65_536, 65_537, 100_000, 131_073, 262_144, 300_007, 524_288, 524_289,
+              1_000_000, 4_000_000, 100_000_000, LIMIT - 1]:
+        chunk = plan.bin_chunk(n, tiles)
+        blocks = plan.bin_blocks(n, chunk)
+        assert blocks * chunk >= n and chunk % plan.bin_threads() == 0
+        # a wave's share of a block is counted in 16 bits, and so is the block's
+        assert 256 <= chunk <= 16384
+        if n <= 256 * 2048 and tiles <= 4096:
+            assert blocks <= 256 and blocks * tiles <= 1 << 20
+        here = plan.bin_matrix_room(n, tiles)
+        assert blocks * tiles <= here and here >= room
+        room = here
