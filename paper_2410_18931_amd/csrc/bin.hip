@@ -188,7 +188,6 @@ __device__ __forceinline__ void prefix_counts(uint32_t* d, int tiles, int tiles_
 // barriers per 256 pairs: at 1 M Gaussians / 1080p counting 43 instead of
 // 18 us, scattering 130 us as before, at 200 k / 720p 21 and 45 instead of 7 and
 // 23 us.)
-constexpr int kTags = 1024;
 
 template <bool SCATTER>
 __global__ __launch_bounds__(kBinThreads) void bin_pass(BinArgs a) {
@@ -269,15 +268,16 @@ __global__ __launch_bounds__(kBinThreads) void bin_pass(BinArgs a) {
       const uint32_t gadj = goff + r.first;  // slot of tile (tx, ty): this + ty w + tx
       expand_pairs(r, mark, lane, [&](bool valid, int owner, uint32_t tx, uint32_t ty, uint32_t w) {
         const uint32_t t = valid ? (ty - ry0) * tiles_x + tx : 0u;
+        const uint32_t own = bin_tag(ty - ry0, tx);
         const uint32_t slot = __shfl(gadj, owner, kWave) + ty * w + tx;
         // Stable rank among the step's pairs of the same tile, where lower
         // lanes hold earlier pairs.  Every lane leaves its number at its
         // tile's tag; those that find another there share the tag, as a rule
         // the tile, and their groups are formed one by one.
-        if (valid) tag[t % kTags] = static_cast<uint8_t>(lane);
+        if (valid) tag[own] = static_cast<uint8_t>(lane);
         wave_lds_fence();
         const uint32_t at = valid ? base[t] + cursor[2 * t] : 0u;
-        uint64_t left = __ballot(valid && tag[t % kTags] != lane);
+        uint64_t left = __ballot(valid && tag[own] != lane);
         uint32_t rank = 0;
         bool last = true;
         while (left) {

@@ -53,6 +53,17 @@ inline GridShape bin_grid(int64_t nblk, int64_t bands, int64_t nv) {
   return {static_cast<uint32_t>((nblk + 7) / 8 * 8), static_cast<uint32_t>(bands), static_cast<uint32_t>(nv)};
 }
 
+// Tag of a band's tile, by which the lanes of a scatter step that place pairs in
+// one tile find each other.  Tiles may share a tag, but every shared one is a
+// step of its own, so the tags lie in rows of kTagPitch, not of the view's tiles:
+// with 128 to 4,096 tiles in a row, powers of two, a splat's rows shared theirs
+// (1 M Gaussians, the stage at 2048 x 1024 and tile 8, 4096 x 2160 and tiles 16
+// and 8, 8192 x 4320 and tile 8: 443, 481, 2,472 and 10,451 us, now 369, 400,
+// 1,571 and 6,277).  An odd pitch above a wave's 64 pairs keeps the pairs that a
+// splat of up to 64 tiles' width has in a step apart.
+constexpr uint32_t kTags = 1024, kTagPitch = 67;
+constexpr uint32_t bin_tag(uint32_t row, uint32_t col) { return (row * kTagPitch + col) % kTags; }
+
 // Pair sums: three lanes for each of `slots` (view, Gaussian)s, in rows of at
 // most 2^22 workgroups.
 constexpr int kSumPerWave = 64 / 3;  // Gaussians of a wave

@@ -21,6 +21,7 @@ void sum_grid(int64_t slots, int64_t* g) {
 int64_t bin_blocks(int64_t n, int64_t chunk) { return wsr::bin_blocks(n, chunk); }
 int64_t bin_chunk(int64_t n, int64_t tiles) { return wsr::bin_chunk(n, tiles); }
 int64_t bin_matrix_room(int64_t n, int64_t tiles) { return wsr::bin_matrix_room(n, tiles); }
+int64_t bin_tag(int64_t row, int64_t col) { return wsr::bin_tag(row, col); }
 int64_t bin_threads() { return wsr::kBinThreads; }
 int64_t sum_waves() { return wsr::kSumWaves; }
 int64_t sum_per_wave() { return wsr::kSumPerWave; }
@@ -37,7 +38,7 @@ def load():
     subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-fPIC", "-shared", "-I",
                     os.path.join(ROOT, "paper_2410_18931_amd", "csrc"), src, "-o", lib], check=True)
     plan = C.CDLL(lib)
-    for name in ("bin_blocks", "bin_chunk", "bin_matrix_room"):
+    for name in ("bin_blocks", "bin_chunk", "bin_matrix_room", "bin_tag"):
         getattr(plan, name).argtypes = [C.c_int64, C.c_int64]
         getattr(plan, name).restype = C.c_int64
     for name in ("bin_threads", "sum_waves", "sum_per_wave"):

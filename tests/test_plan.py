@@ -53,3 +53,18 @@ def test_binning_blocks(tiles):
         here = plan.bin_matrix_room(n, tiles)
         assert blocks * tiles <= here and here >= room
         room = here
+
+
+def test_tags_of_a_splat():
+    """The up to 64 pairs that a splat has in one step of the scatter (a piece
+    of its rectangle, row by row) have tags of their own, wherever it lies."""
+    plan = plan_lib.load()
+    tag = {(r, c): plan.bin_tag(r, c) for r in range(66) for c in range(128)}
+    assert 0 <= min(tag.values()) and max(tag.values()) < 1024
+    for width in range(1, 65):
+        for first in range(width):
+            at = [divmod(first + i, width) for i in range(64)]
+            assert len({tag[x] for x in at}) == 64, (width, first)
+    # a shift of the splat shifts all of its tags alike
+    assert all((plan.bin_tag(r + 5, c + 9) - plan.bin_tag(r, c)) % 1024 == plan.bin_tag(5, 9)
+               for r in range(0, 60, 7) for c in range(0, 4096, 131))
