@@ -1,5 +1,6 @@
 // C-ABI entry points of the WSR library (declared in include/wsr.h): argument
 // checks, workspace layout, and the launch sequence of each step.
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 
@@ -88,6 +89,7 @@ bool make_layout(int64_t n, const wsr_camera* cams, int32_t nv, int32_t tile, La
     const wsr_camera& c = cams[v];
     if (c.width < 1 || c.height < 1 || c.width > 32767 || c.height > 32767) return false;
     if (!(c.fx > 0.f) || !(c.fy > 0.f)) return false;
+    L->max_tiles_y = std::max(L->max_tiles_y, (c.height + tile - 1) / tile);
     tiles += static_cast<int64_t>((c.width + tile - 1) / tile) * ((c.height + tile - 1) / tile);
   }
   if (tiles > 0x7fffffffLL) return false;
@@ -99,8 +101,9 @@ bool make_layout(int64_t n, const wsr_camera* cams, int32_t nv, int32_t tile, La
   for (int v = 0; v < nv; ++v) {
     const wsr_camera& c = cams[v];
     const int tx = (c.width + tile - 1) / tile, ty = (c.height + tile - 1) / tile;
-    if (tx > L->max_tiles_x) L->max_tiles_x = tx;
-    if (ty > L->max_tiles_y) L->max_tiles_y = ty;
+    const int rows = std::min(bin_rows(tx, L->max_tiles_y), ty);
+    L->bands = std::max(L->bands, (ty + rows - 1) / rows);
+    L->band_tiles = std::max(L->band_tiles, rows * tx);
     if (dc) {
       DevCamera& d = dc[v];
       std::memset(&d, 0, sizeof(d));

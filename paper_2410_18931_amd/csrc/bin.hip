@@ -63,7 +63,7 @@ struct BinArgs {
   uint2* ent;                  // list entries (id, Gaussian-major slot)
   int64_t n;
   int64_t capacity;
-  int32_t rows_per_chunk;
+  int32_t max_tiles_y;
   int32_t nblk;                // blocks per view
   int32_t chunk;               // Gaussians per block, a multiple of kBinThreads
   uint32_t* parts;             // per (view, block): sum of the rectangle sizes, then its exclusive scan
@@ -204,9 +204,9 @@ __global__ __launch_bounds__(kBinThreads) void bin_pass(BinArgs a) {
   const DevCamera& cam = a.cams[v];
   const int tiles_x = cam.tiles_x;
   const int tiles_v = cam.tiles_x * cam.tiles_y;
-  const int ry0 = z * a.rows_per_chunk;
+  const int rows = bin_rows(tiles_x, a.max_tiles_y), ry0 = z * rows;
   if (ry0 >= cam.tiles_y) return;
-  const int ry1 = min(ry0 + a.rows_per_chunk, cam.tiles_y);
+  const int ry1 = min(ry0 + rows, cam.tiles_y);
   const int chunk_tiles = (ry1 - ry0) * tiles_x;
   const int t0 = ry0 * tiles_x;  // first tile (view-local) of the band
   uint32_t* row = a.hist + cam.hist_base + static_cast<int64_t>(b) * tiles_v + t0;
@@ -542,19 +542,9 @@ hipError_t launch_bin(const Layout& L, void* ws, void* pairs, int64_t capacity, 
   a.parts = parts;
   a.goff = goff;
   a.chunk = L.bin_chunk;
-  // whole tile rows per band, at most kTileChunk tiles, and at least kBinBands
-  // bands: each block then expands only the pairs of its band, and the more
-  // blocks keep more of the chip busy (the stage at 1 M Gaussians / 1080p,
-  // 200 k / 720p, 300 k / 1001 x 747 and 16 views: 166, 48, 52 and 1,273 us with
-  // 4 bands, 161, 46, 52 and 1,267 us with 6, 161, 47, 58 and 1,264 us with 8,
-  // 165, 52, 62 and 1,352 us with 12)
-  constexpr int kBinBands = 6;
-  if (kTileChunk / L.max_tiles_x < 1) return hipErrorInvalidValue;
-  a.rows_per_chunk = min(kTileChunk / L.max_tiles_x, (L.max_tiles_y + kBinBands - 1) / kBinBands);
-  if (a.rows_per_chunk < 1) a.rows_per_chunk = 1;
-  const int nchunks = (L.max_tiles_y + a.rows_per_chunk - 1) / a.rows_per_chunk;
-  const size_t lds = static_cast<size_t>(a.rows_per_chunk) * L.max_tiles_x * sizeof(uint32_t);
-  const GridShape gs = bin_grid(L.nblk, nchunks, L.nv);
+  a.max_tiles_y = L.max_tiles_y;
+  const size_t lds = static_cast<size_t>(L.band_tiles) * sizeof(uint32_t);
+  const GridShape gs = bin_grid(L.nblk, L.bands, L.nv);
   const dim3 grid(gs.x, gs.y, gs.z);
 
   hipError_t e;

@@ -53,6 +53,20 @@ inline GridShape bin_grid(int64_t nblk, int64_t bands, int64_t nv) {
   return {static_cast<uint32_t>((nblk + 7) / 8 * 8), static_cast<uint32_t>(bands), static_cast<uint32_t>(nv)};
 }
 
+// Tile rows of a band of a view: at most kTileChunk tiles, which share the
+// scatter's LDS at 12 bytes each (57 KB), and at least kBinBands bands for the
+// tallest view: each block then expands only the pairs of its band, and the more
+// blocks keep more of the chip busy (the stage at 1 M Gaussians / 1080p,
+// 200 k / 720p, 300 k / 1001 x 747 and 16 views: 166, 48, 52 and 1,273 us with
+// 4 bands, 161, 46, 52 and 1,267 us with 6, 161, 47, 58 and 1,264 us with 8,
+// 165, 52, 62 and 1,352 us with 12).  The first limit is each view's own: a wide
+// view beside a tall one must not cut the tall one into bands of one row.
+constexpr int32_t kTileChunk = 4864, kBinBands = 6;
+constexpr int32_t bin_rows(int32_t tiles_x, int32_t max_tiles_y) {
+  const int32_t fit = kTileChunk / tiles_x, even = (max_tiles_y + kBinBands - 1) / kBinBands;
+  return fit < 1 ? 1 : fit < even ? fit : even;
+}
+
 // Tag of a band's tile, by which the lanes of a scatter step that place pairs in
 // one tile find each other.  Tiles may share a tag, but every shared one is a
 // step of its own, so the tags lie in rows of kTagPitch, not of the view's tiles:

@@ -10,7 +10,6 @@
 namespace wsr {
 
 constexpr int kWave = 64;
-constexpr int kTileChunk = 4864;      // tiles per binning band (12 bytes of LDS each in the scatter: 57 KB)
 constexpr int kItemSplats = 2048;     // a tile's list is split into raster work items of at most this many
 constexpr int kProjBlock = 256;
 
@@ -101,8 +100,9 @@ struct Layout {
   int32_t tile = 16;
   int32_t bin_chunk = 256;   // Gaussians per binning block
   int32_t nblk = 1;          // binning blocks per view = ceil(n / bin_chunk)
-  int32_t max_tiles_x = 1;
   int32_t max_tiles_y = 1;
+  int32_t bands = 1;         // binning bands of the view that has most
+  int32_t band_tiles = 1;    // tiles of the largest band
   int64_t total_tiles = 0;
   int64_t total_pixels = 0;
   int64_t hist_len = 0;      // entries of the count matrix (without the trailing total)

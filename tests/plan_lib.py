@@ -22,6 +22,7 @@ int64_t bin_blocks(int64_t n, int64_t chunk) { return wsr::bin_blocks(n, chunk);
 int64_t bin_chunk(int64_t n, int64_t tiles) { return wsr::bin_chunk(n, tiles); }
 int64_t bin_matrix_room(int64_t n, int64_t tiles) { return wsr::bin_matrix_room(n, tiles); }
 int64_t bin_tag(int64_t row, int64_t col) { return wsr::bin_tag(row, col); }
+int64_t bin_rows(int64_t tiles_x, int64_t max_tiles_y) { return wsr::bin_rows(tiles_x, max_tiles_y); }
 int64_t bin_threads() { return wsr::kBinThreads; }
 int64_t sum_waves() { return wsr::kSumWaves; }
 int64_t sum_per_wave() { return wsr::kSumPerWave; }
@@ -38,7 +39,7 @@ def load():
     subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-fPIC", "-shared", "-I",
                     os.path.join(ROOT, "paper_2410_18931_amd", "csrc"), src, "-o", lib], check=True)
     plan = C.CDLL(lib)
-    for name in ("bin_blocks", "bin_chunk", "bin_matrix_room", "bin_tag"):
+    for name in ("bin_blocks", "bin_chunk", "bin_matrix_room", "bin_tag", "bin_rows"):
         getattr(plan, name).argtypes = [C.c_int64, C.c_int64]
         getattr(plan, name).restype = C.c_int64
     for name in ("bin_threads", "sum_waves", "sum_per_wave"):

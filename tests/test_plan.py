@@ -68,3 +68,17 @@ def test_tags_of_a_splat():
     # a shift of the splat shifts all of its tags alike
     assert all((plan.bin_tag(r + 5, c + 9) - plan.bin_tag(r, c)) % 1024 == plan.bin_tag(5, 9)
                for r in range(0, 60, 7) for c in range(0, 4096, 131))
+
+
+@pytest.mark.parametrize("views", [[(1, 1)], [(8, 8)], [(120, 68)], [(4096, 3), (8, 4096)], [(4096, 4096)], [(1, 4096), (2, 5)],
+                                   [(480, 270)], [(4096, 8), (8, 4096)], [(16, 9), (240, 135)]])
+def test_binning_bands(views):
+    """A band fits the scatter's LDS (12 bytes a tile beside 5,136 bytes of
+    marks, tags and sums, 64 KB in all), and is as high as its own view's width
+    allows up to a sixth of the tallest view's rows."""
+    plan = plan_lib.load()
+    tallest = max(ty for _, ty in views)
+    for tx, ty in views:
+        rows = plan.bin_rows(tx, tallest)
+        assert rows >= 1 and 12 * rows * tx + 5136 <= 65536
+        assert rows == (tallest + 5) // 6 or (rows + 1) * tx > 4864
