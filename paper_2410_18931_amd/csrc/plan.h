@@ -26,8 +26,14 @@ struct GridShape {
 // 128 x 128 takes 50, 52 and 67 us with at most 256, 512 and 1,024 blocks
 // (101 without a limit, 63 in blocks of 2,048 throughout), for 300 k in twelve
 // views of 200 x 133 166, 177 and 211 us.
-constexpr int32_t kBinChunkMin = 256, kBinChunkMax = 2048;
-constexpr int64_t kBinSmall = 1 << 20, kBinBlocks = 256;
+//
+// Where the matrix has more than kBinLarge entries even so, what a block does for
+// every tile (its counts, their prefix sums, its row of the matrix) is most of
+// the stage, and blocks of 4,096 halve it: 1 M Gaussians at 3840 x 2160 and tiles
+// 16 and 8 386 -> 340 and 1,466 -> 1,117 us (372 and 1,907 before rectangles were
+// counted by their corners), at 7680 x 4320 and tile 16 1,470 -> 1,113 us.
+constexpr int32_t kBinChunkMin = 256, kBinChunkMax = 2048, kBinChunkLarge = 4096;
+constexpr int64_t kBinSmall = 1 << 20, kBinLarge = 12 << 20, kBinBlocks = 256;
 
 inline int64_t bin_blocks(int64_t n, int64_t chunk) { return n > 0 ? (n + chunk - 1) / chunk : 1; }
 
@@ -35,14 +41,15 @@ inline int32_t bin_chunk(int64_t n, int64_t tiles) {
   int32_t chunk = kBinChunkMin;
   while (chunk < kBinChunkMax && (bin_blocks(n, chunk) > kBinBlocks || bin_blocks(n, chunk) * tiles > kBinSmall))
     chunk *= 2;
+  if (chunk == kBinChunkMax && bin_blocks(n, chunk) * tiles > kBinLarge) chunk = kBinChunkLarge;
   return chunk;
 }
 
 // Entries to hold the count matrix of every Gaussian count up to n: a workspace
 // never holds fewer Gaussians than it was sized for.
 inline int64_t bin_matrix_room(int64_t n, int64_t tiles) {
-  const int64_t most = bin_blocks(n, kBinChunkMin) * tiles;
-  return std::max(bin_blocks(n, kBinChunkMax) * tiles, std::min(most, kBinSmall));
+  auto upto = [&](int32_t chunk, int64_t limit) { return std::min(bin_blocks(n, chunk) * tiles, limit); };
+  return std::max({upto(kBinChunkMin, kBinSmall), upto(kBinChunkMax, kBinLarge), bin_blocks(n, kBinChunkLarge) * tiles});
 }
 
 // Binning passes: x the blocks of a view, rounded up to whole eighths (one for

@@ -50,6 +50,7 @@ def test_binning_blocks(tiles):
         assert 256 <= chunk <= 16384
         if n <= 256 * 2048 and tiles <= 4096:
             assert blocks <= 256 and blocks * tiles <= 1 << 20
+        assert blocks * tiles <= 12 << 20 or chunk == 4096  # nor 12 x 2^20 with blocks of less than 4,096
         here = plan.bin_matrix_room(n, tiles)
         assert blocks * tiles <= here and here >= room
         room = here
