@@ -84,18 +84,20 @@ bool make_layout(int64_t n, const wsr_camera* cams, int32_t nv, int32_t tile, La
   L->n = n;
   L->nv = nv;
   L->tile = tile;
-  int64_t tiles = 0, pixels = 0;
+  int64_t tiles = 0, largest = 0, pixels = 0;
   for (int v = 0; v < nv; ++v) {
     const wsr_camera& c = cams[v];
     if (c.width < 1 || c.height < 1 || c.width > 32767 || c.height > 32767) return false;
     if (!(c.fx > 0.f) || !(c.fy > 0.f)) return false;
     L->max_tiles_y = std::max(L->max_tiles_y, (c.height + tile - 1) / tile);
-    tiles += static_cast<int64_t>((c.width + tile - 1) / tile) * ((c.height + tile - 1) / tile);
+    const int64_t t = static_cast<int64_t>((c.width + tile - 1) / tile) * ((c.height + tile - 1) / tile);
+    largest = std::max(largest, t);
+    tiles += t;
   }
   if (tiles > 0x7fffffffLL) return false;
-  L->bin_chunk = bin_chunk(n, tiles);
+  L->bin_chunk = bin_chunk(n, tiles, largest);
   L->nblk = static_cast<int32_t>(bin_blocks(n, L->bin_chunk));
-  const int64_t hist_room = bin_matrix_room(n, tiles);
+  const int64_t hist_room = bin_matrix_room(n, tiles, largest);
   int64_t hist = 0;
   tiles = 0;
   for (int v = 0; v < nv; ++v) {
@@ -114,6 +116,8 @@ bool make_layout(int64_t n, const wsr_camera* cams, int32_t nv, int32_t tile, La
       d.fx = c.fx; d.fy = c.fy; d.cx = c.cx; d.cy = c.cy;
       d.width = c.width; d.height = c.height;
       d.tiles_x = tx; d.tiles_y = ty;
+      d.band_rows = static_cast<uint16_t>(rows);
+      d.tag_pitch = static_cast<uint16_t>(bin_tag_pitch(tx));
       d.tile_base = static_cast<int32_t>(tiles);
       d.pix_base = pixels;
       d.hist_base = hist;

@@ -63,7 +63,6 @@ struct BinArgs {
   uint2* ent;                  // list entries (id, Gaussian-major slot)
   int64_t n;
   int64_t capacity;
-  int32_t max_tiles_y;
   int32_t nblk;                // blocks per view
   int32_t chunk;               // Gaussians per block, a multiple of kBinThreads
   uint32_t* parts;             // per (view, block): sum of the rectangle sizes, then its exclusive scan
@@ -204,7 +203,7 @@ __global__ __launch_bounds__(kBinThreads) void bin_pass(BinArgs a) {
   const DevCamera& cam = a.cams[v];
   const int tiles_x = cam.tiles_x;
   const int tiles_v = cam.tiles_x * cam.tiles_y;
-  const int rows = bin_rows(tiles_x, a.max_tiles_y), ry0 = z * rows;
+  const int rows = cam.band_rows, ry0 = z * rows;
   if (ry0 >= cam.tiles_y) return;
   const int ry1 = min(ry0 + rows, cam.tiles_y);
   const int chunk_tiles = (ry1 - ry0) * tiles_x;
@@ -246,6 +245,7 @@ __global__ __launch_bounds__(kBinThreads) void bin_pass(BinArgs a) {
     __shared__ uint8_t s_tag[kBinWaves][kTags];
     uint32_t* mark = s_mark[wv];
     uint8_t* tag = s_tag[wv];
+    const uint32_t pitch = cam.tag_pitch;
     // counts of waves 0 to 3 -> their first places
     for (int t = threadIdx.x; t < chunk_tiles; t += kBinThreads) {
       const uint32_t c0 = counts[t] & 0xffffu, c1 = counts[t] >> 16, c2 = counts[chunk_tiles + t] & 0xffffu;
@@ -267,9 +267,11 @@ __global__ __launch_bounds__(kBinThreads) void bin_pass(BinArgs a) {
       if (z == 0 && g + lane < g1) a.goff[static_cast<int64_t>(v) * a.n + g + lane] = goff;
       const uint32_t gadj = goff + r.first;  // slot of tile (tx, ty): this + ty w + tx
       expand_pairs(r, mark, lane, [&](bool valid, int owner, uint32_t tx, uint32_t ty, uint32_t w) {
-        const uint32_t t = valid ? (ty - ry0) * tiles_x + tx : 0u;
-        const uint32_t own = bin_tag(ty - ry0, tx);
-        const uint32_t slot = __shfl(gadj, owner, kWave) + ty * w + tx;
+        // (24-bit products, at the full rate)
+        const uint32_t tr = ty - ry0;
+        const uint32_t t = valid ? __umul24(tr, tiles_x) + tx : 0u;
+        const uint32_t own = (__umul24(tr, pitch) + tx) % kTags;
+        const uint32_t slot = __shfl(gadj, owner, kWave) + __umul24(ty, w) + tx;
         // Stable rank among the step's pairs of the same tile, where lower
         // lanes hold earlier pairs.  Every lane leaves its number at its
         // tile's tag; those that find another there share the tag, as a rule
@@ -542,7 +544,6 @@ hipError_t launch_bin(const Layout& L, void* ws, void* pairs, int64_t capacity, 
   a.parts = parts;
   a.goff = goff;
   a.chunk = L.bin_chunk;
-  a.max_tiles_y = L.max_tiles_y;
   const size_t lds = static_cast<size_t>(L.band_tiles) * sizeof(uint32_t);
   const GridShape gs = bin_grid(L.nblk, L.bands, L.nv);
   const dim3 grid(gs.x, gs.y, gs.z);

@@ -27,7 +27,7 @@ struct GridShape {
 // (101 without a limit, 63 in blocks of 2,048 throughout), for 300 k in twelve
 // views of 200 x 133 166, 177 and 211 us.
 //
-// Where the matrix has more than kBinLarge entries even so, what a block does for
+// Where a view's part of the matrix has more than kBinLarge entries even so, what a block does for
 // every tile (its counts, their prefix sums, its row of the matrix) is most of
 // the stage, and blocks of 4,096 halve it: 1 M Gaussians at 3840 x 2160 and tiles
 // 16 and 8 386 -> 340 and 1,466 -> 1,117 us (372 and 1,907 before rectangles were
@@ -37,19 +37,21 @@ constexpr int64_t kBinSmall = 1 << 20, kBinLarge = 12 << 20, kBinBlocks = 256;
 
 inline int64_t bin_blocks(int64_t n, int64_t chunk) { return n > 0 ? (n + chunk - 1) / chunk : 1; }
 
-inline int32_t bin_chunk(int64_t n, int64_t tiles) {
+// tiles: of all views; largest: of the view that has most
+inline int32_t bin_chunk(int64_t n, int64_t tiles, int64_t largest) {
   int32_t chunk = kBinChunkMin;
   while (chunk < kBinChunkMax && (bin_blocks(n, chunk) > kBinBlocks || bin_blocks(n, chunk) * tiles > kBinSmall))
     chunk *= 2;
-  if (chunk == kBinChunkMax && bin_blocks(n, chunk) * tiles > kBinLarge) chunk = kBinChunkLarge;
+  if (chunk == kBinChunkMax && bin_blocks(n, chunk) * largest > kBinLarge) chunk = kBinChunkLarge;
   return chunk;
 }
 
 // Entries to hold the count matrix of every Gaussian count up to n: a workspace
 // never holds fewer Gaussians than it was sized for.
-inline int64_t bin_matrix_room(int64_t n, int64_t tiles) {
-  auto upto = [&](int32_t chunk, int64_t limit) { return std::min(bin_blocks(n, chunk) * tiles, limit); };
-  return std::max({upto(kBinChunkMin, kBinSmall), upto(kBinChunkMax, kBinLarge), bin_blocks(n, kBinChunkLarge) * tiles});
+inline int64_t bin_matrix_room(int64_t n, int64_t tiles, int64_t largest) {
+  const int64_t small = std::min(bin_blocks(n, kBinChunkMin) * tiles, kBinSmall);
+  const int64_t most = std::min(bin_blocks(n, kBinChunkMax), kBinLarge / largest);
+  return std::max({small, most * tiles, bin_blocks(n, kBinChunkLarge) * tiles});
 }
 
 // Binning passes: x the blocks of a view, rounded up to whole eighths (one for
@@ -76,14 +78,30 @@ constexpr int32_t bin_rows(int32_t tiles_x, int32_t max_tiles_y) {
 
 // Tag of a band's tile, by which the lanes of a scatter step that place pairs in
 // one tile find each other.  Tiles may share a tag, but every shared one is a
-// step of its own, so the tags lie in rows of kTagPitch, not of the view's tiles:
-// with 128 to 4,096 tiles in a row, powers of two, a splat's rows shared theirs
+// step of its own, so the tags of the pairs that one splat has in a step, up to
+// 64 tiles of its rectangle row by row, are kept apart: the k-th row after one
+// lies k pitches further on, modulo the number of tags, and as both are in the
+// step only if a row has fewer than 64 / (k - 1) tiles, as many tags between them
+// are enough.  The pitch is the view's width where that holds, which spreads a
+// band's tiles best, and else the next larger one where it does.  Among the widths where it does not hold are the powers of two
 // (1 M Gaussians, the stage at 2048 x 1024 and tile 8, 4096 x 2160 and tiles 16
-// and 8, 8192 x 4320 and tile 8: 443, 481, 2,472 and 10,451 us, now 369, 400,
-// 1,571 and 6,277).  An odd pitch above a wave's 64 pairs keeps the pairs that a
-// splat of up to 64 tiles' width has in a step apart.
-constexpr uint32_t kTags = 1024, kTagPitch = 67;
-constexpr uint32_t bin_tag(uint32_t row, uint32_t col) { return (row * kTagPitch + col) % kTags; }
+// and 8, 8192 x 4320 and tile 8, with tags by width and as now: @@).  A pitch of 67 throughout costs 149 instead of
+// 142 us at 1080p, where a band's 12 rows of 120 tiles then share 857 tags.
+constexpr uint32_t kTags = 1024;
+constexpr uint32_t bin_tag(uint32_t row, uint32_t col, uint32_t pitch) { return (row * pitch + col) % kTags; }
+
+inline int32_t bin_tag_pitch(int32_t tiles_x) {
+  auto apart = [&](int32_t pitch) {
+    for (int32_t k = 1; k < 64; ++k) {
+      const int32_t far = k * pitch % static_cast<int32_t>(kTags);
+      if (std::min(far, static_cast<int32_t>(kTags) - far) < std::min(tiles_x, k == 1 ? 64 : 63 / (k - 1))) return false;
+    }
+    return true;
+  };
+  int32_t pitch = tiles_x;
+  while (!apart(pitch)) ++pitch;
+  return pitch;
+}
 
 // Pair sums: three lanes for each of `slots` (view, Gaussian)s, in rows of at
 // most 2^22 workgroups.

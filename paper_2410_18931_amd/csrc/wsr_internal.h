@@ -22,7 +22,8 @@ struct DevCamera {
   int32_t width, height;
   int32_t tiles_x, tiles_y;
   int32_t tile_base;   // first global tile index of this view
-  int32_t pad0;
+  uint16_t band_rows;  // tile rows of a binning band (see bin_rows)
+  uint16_t tag_pitch;  // row pitch of the binning's tags (see bin_tag)
   int64_t pix_base;    // first pixel of this view in the concatenated images
   int64_t hist_base;   // first entry of this view in the (block, tile) count matrix
 };

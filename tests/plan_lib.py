@@ -19,9 +19,22 @@ void sum_grid(int64_t slots, int64_t* g) {
   g[0] = s.x; g[1] = s.y; g[2] = s.z;
 }
 int64_t bin_blocks(int64_t n, int64_t chunk) { return wsr::bin_blocks(n, chunk); }
-int64_t bin_chunk(int64_t n, int64_t tiles) { return wsr::bin_chunk(n, tiles); }
-int64_t bin_matrix_room(int64_t n, int64_t tiles) { return wsr::bin_matrix_room(n, tiles); }
-int64_t bin_tag(int64_t row, int64_t col) { return wsr::bin_tag(row, col); }
+int64_t bin_chunk(int64_t n, int64_t tiles, int64_t largest) { return wsr::bin_chunk(n, tiles, largest); }
+int64_t bin_matrix_room(int64_t n, int64_t tiles, int64_t largest) { return wsr::bin_matrix_room(n, tiles, largest); }
+int64_t bin_tag_pitch(int64_t tiles_x) { return wsr::bin_tag_pitch(tiles_x); }
+// pairs of one step of a splat `width` tiles wide that share a tag
+int64_t shared_tags(int64_t width, int64_t pitch) {
+  int64_t shared = 0;
+  for (int64_t first = 0; first < width; ++first) {
+    bool seen[wsr::kTags] = {};
+    for (int64_t i = first; i < first + 64; ++i) {
+      bool& s = seen[wsr::bin_tag(i / width, i % width, pitch)];
+      shared += s;
+      s = true;
+    }
+  }
+  return shared;
+}
 int64_t bin_rows(int64_t tiles_x, int64_t max_tiles_y) { return wsr::bin_rows(tiles_x, max_tiles_y); }
 int64_t bin_threads() { return wsr::kBinThreads; }
 int64_t sum_waves() { return wsr::kSumWaves; }
@@ -39,11 +52,12 @@ def load():
     subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-fPIC", "-shared", "-I",
                     os.path.join(ROOT, "paper_2410_18931_amd", "csrc"), src, "-o", lib], check=True)
     plan = C.CDLL(lib)
-    for name in ("bin_blocks", "bin_chunk", "bin_matrix_room", "bin_tag", "bin_rows"):
-        getattr(plan, name).argtypes = [C.c_int64, C.c_int64]
+    for name in ("bin_blocks", "bin_rows", "shared_tags", "bin_chunk", "bin_matrix_room"):
+        getattr(plan, name).argtypes = [C.c_int64] * (3 if name in ("bin_chunk", "bin_matrix_room") else 2)
         getattr(plan, name).restype = C.c_int64
-    for name in ("bin_threads", "sum_waves", "sum_per_wave"):
+    for name in ("bin_tag_pitch", "bin_threads", "sum_waves", "sum_per_wave"):
         getattr(plan, name).restype = C.c_int64
+    plan.bin_tag_pitch.argtypes = [C.c_int64]
     plan.bin_grid.argtypes = [C.c_int64, C.c_int64, C.c_int64, C.c_void_p]
     plan.sum_grid.argtypes = [C.c_int64, C.c_void_p]
     return plan

@@ -34,41 +34,40 @@ def test_pair_sum_grid(slots):
         assert (x, y) == ((slots + per - 1) // per, 1)
 
 
-@pytest.mark.parametrize("tiles", [1, 64, 104, 920, 3600, 8160, 60_000, 129_600, 16_777_216])
-def test_binning_blocks(tiles):
+@pytest.mark.parametrize("tiles,views", [(1, 1), (64, 1), (104, 12), (920, 1), (3600, 1), (8160, 1), (60_000, 16),
+                                         (129_600, 1), (129_600, 4), (16_777_216, 1), (16_777_216, 256), (65, 64)])
+def test_binning_blocks(tiles, views):
     """Blocks grow before their number, the length of a column of the count
     matrix, passes 256 or the matrix 2^20 entries, and no workspace has less
     room than a smaller Gaussian count needs."""
     plan = plan_lib.load()
-    room = 0
-    for n in [0, 1, 255, 256, 257, 4096, 30_011, 65_536, 65_537, 100_000, 131_073, 262_144, 300_007, 524_288, 524_289,
-              1_000_000, 4_000_000, 100_000_000, LIMIT - 1]:
-        chunk = plan.bin_chunk(n, tiles)
+    room, largest = 0, (tiles + views - 1) // views
+    for n in sorted([0, 1, 255, 256, 257, 4096, 30_011, 65_536, 65_537, 100_000, 131_073, 262_144, 300_007, 524_288, 524_289,
+              1_000_000, 4_000_000, 100_000_000, LIMIT - 1] + list(range(2000, 6_000_000, 65_521))):
+        chunk = plan.bin_chunk(n, tiles, largest)
         blocks = plan.bin_blocks(n, chunk)
         assert blocks * chunk >= n and chunk % plan.bin_threads() == 0
         # a wave's share of a block is counted in 16 bits, and so is the block's
         assert 256 <= chunk <= 16384
         if n <= 256 * 2048 and tiles <= 4096:
             assert blocks <= 256 and blocks * tiles <= 1 << 20
-        assert blocks * tiles <= 12 << 20 or chunk == 4096  # nor 12 x 2^20 with blocks of less than 4,096
-        here = plan.bin_matrix_room(n, tiles)
+        assert blocks * largest <= 12 << 20 or chunk == 4096  # nor a view's part 12 x 2^20 in blocks of less than 4,096
+        here = plan.bin_matrix_room(n, tiles, largest)
         assert blocks * tiles <= here and here >= room
         room = here
 
 
 def test_tags_of_a_splat():
     """The up to 64 pairs that a splat has in one step of the scatter (a piece
-    of its rectangle, row by row) have tags of their own, wherever it lies."""
+    of its rectangle, row by row) have tags of their own in a view of any width."""
     plan = plan_lib.load()
-    tag = {(r, c): plan.bin_tag(r, c) for r in range(66) for c in range(128)}
-    assert 0 <= min(tag.values()) and max(tag.values()) < 1024
-    for width in range(1, 65):
-        for first in range(width):
-            at = [divmod(first + i, width) for i in range(64)]
-            assert len({tag[x] for x in at}) == 64, (width, first)
-    # a shift of the splat shifts all of its tags alike
-    assert all((plan.bin_tag(r + 5, c + 9) - plan.bin_tag(r, c)) % 1024 == plan.bin_tag(5, 9)
-               for r in range(0, 60, 7) for c in range(0, 4096, 131))
+    for tiles_x in list(range(1, 700)) + list(range(1016, 1032)) + [2047, 2048, 2049, 4095, 4096]:
+        pitch = plan.bin_tag_pitch(tiles_x)
+        assert tiles_x <= pitch < tiles_x + 128
+        for width in list(range(1, min(tiles_x, 64) + 1)) + ([tiles_x // 2 + 1, tiles_x] if tiles_x < 900 else []):
+            assert plan.shared_tags(width, pitch) == 0, (tiles_x, pitch, width)
+    # most views keep their own width
+    assert all(plan.bin_tag_pitch(t) == t for t in (26, 40, 80, 120, 240)) and plan.bin_tag_pitch(256) > 256
 
 
 @pytest.mark.parametrize("views", [[(1, 1)], [(8, 8)], [(120, 68)], [(4096, 3), (8, 4096)], [(4096, 4096)], [(1, 4096), (2, 5)],
