@@ -187,8 +187,9 @@ __device__ __forceinline__ void prefix_counts(uint32_t* d, int tiles, int tiles_
 // barriers per 256 pairs: at 1 M Gaussians / 1080p counting 43 instead of
 // 18 us, scattering 130 us as before, at 200 k / 720p 21 and 45 instead of 7 and
 // 23 us.)
-
-template <bool SCATTER>
+//
+// FEW: bands of at most kFewTiles tiles (see plan.h).
+template <bool SCATTER, bool FEW>
 __global__ __launch_bounds__(kBinThreads) void bin_pass(BinArgs a) {
   extern __shared__ uint32_t lds[];
   __shared__ uint32_t s_full[kBinWaves];
@@ -242,9 +243,9 @@ __global__ __launch_bounds__(kBinThreads) void bin_pass(BinArgs a) {
     if (z == 0 && threadIdx.x == 0) a.parts[part] = s_full[0] + s_full[1] + s_full[2] + s_full[3];
   } else {
     __shared__ uint32_t s_mark[kBinWaves][kWave];
-    __shared__ uint8_t s_tag[kBinWaves][kTags];
+    __shared__ uint8_t s_tag[FEW ? 1 : kBinWaves][kTags];
     uint32_t* mark = s_mark[wv];
-    uint8_t* tag = s_tag[wv];
+    uint8_t* tag = s_tag[FEW ? 0 : wv];
     const uint32_t pitch = cam.tag_pitch;
     // counts of waves 0 to 3 -> their first places
     for (int t = threadIdx.x; t < chunk_tiles; t += kBinThreads) {
@@ -270,26 +271,40 @@ __global__ __launch_bounds__(kBinThreads) void bin_pass(BinArgs a) {
         // (24-bit products, at the full rate)
         const uint32_t tr = ty - ry0;
         const uint32_t t = valid ? __umul24(tr, tiles_x) + tx : 0u;
-        const uint32_t own = (__umul24(tr, pitch) + tx) % kTags;
         const uint32_t slot = __shfl(gadj, owner, kWave) + __umul24(ty, w) + tx;
         // Stable rank among the step's pairs of the same tile, where lower
-        // lanes hold earlier pairs.  Every lane leaves its number at its
-        // tile's tag; those that find another there share the tag, as a rule
-        // the tile, and their groups are formed one by one.
-        if (valid) tag[own] = static_cast<uint8_t>(lane);
-        wave_lds_fence();
-        const uint32_t at = valid ? base[t] + cursor[2 * t] : 0u;
-        uint64_t left = __ballot(valid && tag[own] != lane);
-        uint32_t rank = 0;
+        // lanes hold earlier pairs.
+        uint32_t at = 0, rank = 0;
         bool last = true;
-        while (left) {
-          const uint32_t tl = __builtin_amdgcn_readlane(t, __ffsll(static_cast<long long>(left)) - 1);
-          const uint64_t same = __ballot(valid && t == tl);
-          if (t == tl) {
-            rank = static_cast<uint32_t>(__popcll(same & ((1ull << lane) - 1ull)));
-            last = (same >> lane) == 1ull;
+        if constexpr (FEW) {
+          uint64_t same = __ballot(valid);
+#pragma unroll
+          for (int k = 0; k < kFewBits; ++k) {
+            const uint64_t ones = __ballot((t >> k) & 1u);
+            same &= (t >> k) & 1u ? ones : ~ones;
           }
-          left &= ~same;
+          rank = static_cast<uint32_t>(__popcll(same & ((1ull << lane) - 1ull)));
+          last = (same >> lane) == 1ull;
+          if (valid) at = base[t] + cursor[2 * t];
+          wave_lds_fence();
+        } else {
+          // Every lane leaves its number at its tile's tag; those that find
+          // another there share the tag, as a rule the tile, and their groups
+          // are formed one by one.
+          const uint32_t own = (__umul24(tr, pitch) + tx) % kTags;
+          if (valid) tag[own] = static_cast<uint8_t>(lane);
+          wave_lds_fence();
+          if (valid) at = base[t] + cursor[2 * t];
+          uint64_t left = __ballot(valid && tag[own] != lane);
+          while (left) {
+            const uint32_t tl = __builtin_amdgcn_readlane(t, __ffsll(static_cast<long long>(left)) - 1);
+            const uint64_t same = __ballot(valid && t == tl);
+            if (t == tl) {
+              rank = static_cast<uint32_t>(__popcll(same & ((1ull << lane) - 1ull)));
+              last = (same >> lane) == 1ull;
+            }
+            left &= ~same;
+          }
         }
         if (valid) {
           const uint32_t pos = at + rank;
@@ -549,7 +564,7 @@ hipError_t launch_bin(const Layout& L, void* ws, void* pairs, int64_t capacity, 
   const dim3 grid(gs.x, gs.y, gs.z);
 
   hipError_t e;
-  bin_pass<false><<<grid, kBinThreads, lds, st>>>(a);
+  bin_pass<false, false><<<grid, kBinThreads, lds, st>>>(a);
   column_scan_wide<<<static_cast<unsigned>((L.total_tiles + 1 + kWave - 1) / kWave), kColWaves * kWave, 0, st>>>(
       a.cams, L.nv, L.nblk, L.total_tiles, hist, tstart);
   if ((e = hipGetLastError()) != hipSuccess) return e;
@@ -560,7 +575,10 @@ hipError_t launch_bin(const Layout& L, void* ws, void* pairs, int64_t capacity, 
                                                    capacity, parts, static_cast<int64_t>(L.nv) * L.nblk,
                                                    goff + L.n * L.nv);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  bin_pass<true><<<grid, kBinThreads, 3 * lds, st>>>(a);
+  if (L.band_tiles <= kFewTiles)
+    bin_pass<true, true><<<grid, kBinThreads, 3 * lds, st>>>(a);
+  else
+    bin_pass<true, false><<<grid, kBinThreads, 3 * lds, st>>>(a);
   return hipGetLastError();
 }
 

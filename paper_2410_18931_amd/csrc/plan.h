@@ -76,6 +76,14 @@ constexpr int32_t bin_rows(int32_t tiles_x, int32_t max_tiles_y) {
   return fit < 1 ? 1 : fit < even ? fit : even;
 }
 
+// In bands of at most kFewTiles tiles many of a scatter step's 64 pairs share a
+// tile, and the lanes of each tile are found bit by bit of its number, in
+// kFewBits ballots, instead of tile by tile (300 k Gaussians in twelve views of
+// 200 x 133, bands of 26 tiles: the stage 171 us tile by tile, 158 bit by bit;
+// 100 k in 64 views of 128 x 128, 16 tiles: 322 and 292; with 33 to 64 tiles both
+// are level).
+constexpr int32_t kFewBits = 5, kFewTiles = 1 << kFewBits;
+
 // Tag of a band's tile, by which the lanes of a scatter step that place pairs in
 // one tile find each other.  Tiles may share a tag, but every shared one is a
 // step of its own, so the tags of the pairs that one splat has in a step, up to
@@ -85,7 +93,8 @@ constexpr int32_t bin_rows(int32_t tiles_x, int32_t max_tiles_y) {
 // are enough.  The pitch is the view's width where that holds, which spreads a
 // band's tiles best, and else the next larger one where it does.  Among the widths where it does not hold are the powers of two
 // (1 M Gaussians, the stage at 2048 x 1024 and tile 8, 4096 x 2160 and tiles 16
-// and 8, 8192 x 4320 and tile 8, with tags by width and as now: @@).  A pitch of 67 throughout costs 149 instead of
+// and 8, 8192 x 4320 and tile 8: 443, 481, 2,472 and 10,451 us with tags by width,
+// 328, 353, 1,147 and 4,784 now).  A pitch of 67 throughout costs 149 instead of
 // 142 us at 1080p, where a band's 12 rows of 120 tiles then share 857 tags.
 constexpr uint32_t kTags = 1024;
 constexpr uint32_t bin_tag(uint32_t row, uint32_t col, uint32_t pitch) { return (row * pitch + col) % kTags; }

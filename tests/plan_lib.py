@@ -36,6 +36,7 @@ int64_t shared_tags(int64_t width, int64_t pitch) {
   return shared;
 }
 int64_t bin_rows(int64_t tiles_x, int64_t max_tiles_y) { return wsr::bin_rows(tiles_x, max_tiles_y); }
+int64_t few_tiles() { return wsr::kFewTiles; }
 int64_t bin_threads() { return wsr::kBinThreads; }
 int64_t sum_waves() { return wsr::kSumWaves; }
 int64_t sum_per_wave() { return wsr::kSumPerWave; }
@@ -55,7 +56,7 @@ def load():
     for name in ("bin_blocks", "bin_rows", "shared_tags", "bin_chunk", "bin_matrix_room"):
         getattr(plan, name).argtypes = [C.c_int64] * (3 if name in ("bin_chunk", "bin_matrix_room") else 2)
         getattr(plan, name).restype = C.c_int64
-    for name in ("bin_tag_pitch", "bin_threads", "sum_waves", "sum_per_wave"):
+    for name in ("bin_tag_pitch", "bin_threads", "few_tiles", "sum_waves", "sum_per_wave"):
         getattr(plan, name).restype = C.c_int64
     plan.bin_tag_pitch.argtypes = [C.c_int64]
     plan.bin_grid.argtypes = [C.c_int64, C.c_int64, C.c_int64, C.c_void_p]
