@@ -95,7 +95,7 @@ bool make_layout(int64_t n, const wsr_camera* cams, int32_t nv, int32_t tile, La
     tiles += t;
   }
   if (tiles > 0x7fffffffLL) return false;
-  L->bin_chunk = bin_chunk(n, tiles, largest);
+  L->bin_chunk = bin_chunk(n, nv, tiles, largest);
   L->nblk = static_cast<int32_t>(bin_blocks(n, L->bin_chunk));
   const int64_t hist_room = bin_matrix_room(n, tiles, largest);
   int64_t hist = 0;

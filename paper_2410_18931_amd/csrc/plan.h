@@ -25,7 +25,9 @@ struct GridShape {
 // small image has nothing to hide behind: the stage for 500 k Gaussians at
 // 128 x 128 takes 50, 52 and 67 us with at most 256, 512 and 1,024 blocks
 // (101 without a limit, 63 in blocks of 2,048 throughout), for 300 k in twelve
-// views of 200 x 133 166, 177 and 211 us.
+// views of 200 x 133 166, 177 and 211 us.  With one view, blocks of 2,048 leave
+// the chip idle, and up to kBinBlocksFull blocks of 1,024 are better (300 k at
+// 1001 x 747, 293 blocks: 53.2 us and 55.4 in blocks of 2,048).
 //
 // Where a view's part of the matrix has more than kBinLarge entries even so, what a block does for
 // every tile (its counts, their prefix sums, its row of the matrix) is most of
@@ -33,14 +35,15 @@ struct GridShape {
 // 16 and 8 386 -> 340 and 1,466 -> 1,117 us (372 and 1,907 before rectangles were
 // counted by their corners), at 7680 x 4320 and tile 16 1,470 -> 1,113 us.
 constexpr int32_t kBinChunkMin = 256, kBinChunkMax = 2048, kBinChunkLarge = 4096;
-constexpr int64_t kBinSmall = 1 << 20, kBinLarge = 12 << 20, kBinBlocks = 256;
+constexpr int64_t kBinSmall = 1 << 20, kBinLarge = 12 << 20, kBinBlocks = 256, kBinBlocksFull = 320;
 
 inline int64_t bin_blocks(int64_t n, int64_t chunk) { return n > 0 ? (n + chunk - 1) / chunk : 1; }
 
 // tiles: of all views; largest: of the view that has most
-inline int32_t bin_chunk(int64_t n, int64_t tiles, int64_t largest) {
+inline int32_t bin_chunk(int64_t n, int64_t views, int64_t tiles, int64_t largest) {
   int32_t chunk = kBinChunkMin;
-  while (chunk < kBinChunkMax && (bin_blocks(n, chunk) > kBinBlocks || bin_blocks(n, chunk) * tiles > kBinSmall))
+  auto most = [&] { return views == 1 && 2 * chunk == kBinChunkMax ? kBinBlocksFull : kBinBlocks; };
+  while (chunk < kBinChunkMax && (bin_blocks(n, chunk) > most() || bin_blocks(n, chunk) * tiles > kBinSmall))
     chunk *= 2;
   if (chunk == kBinChunkMax && bin_blocks(n, chunk) * largest > kBinLarge) chunk = kBinChunkLarge;
   return chunk;

@@ -19,7 +19,9 @@ void sum_grid(int64_t slots, int64_t* g) {
   g[0] = s.x; g[1] = s.y; g[2] = s.z;
 }
 int64_t bin_blocks(int64_t n, int64_t chunk) { return wsr::bin_blocks(n, chunk); }
-int64_t bin_chunk(int64_t n, int64_t tiles, int64_t largest) { return wsr::bin_chunk(n, tiles, largest); }
+int64_t bin_chunk(int64_t n, int64_t views, int64_t tiles, int64_t largest) {
+  return wsr::bin_chunk(n, views, tiles, largest);
+}
 int64_t bin_matrix_room(int64_t n, int64_t tiles, int64_t largest) { return wsr::bin_matrix_room(n, tiles, largest); }
 int64_t bin_tag_pitch(int64_t tiles_x) { return wsr::bin_tag_pitch(tiles_x); }
 // pairs of one step of a splat `width` tiles wide that share a tag
@@ -54,7 +56,7 @@ def load():
                     os.path.join(ROOT, "paper_2410_18931_amd", "csrc"), src, "-o", lib], check=True)
     plan = C.CDLL(lib)
     for name in ("bin_blocks", "bin_rows", "shared_tags", "bin_chunk", "bin_matrix_room"):
-        getattr(plan, name).argtypes = [C.c_int64] * (3 if name in ("bin_chunk", "bin_matrix_room") else 2)
+        getattr(plan, name).argtypes = [C.c_int64] * {"bin_chunk": 4, "bin_matrix_room": 3}.get(name, 2)
         getattr(plan, name).restype = C.c_int64
     for name in ("bin_tag_pitch", "bin_threads", "few_tiles", "sum_waves", "sum_per_wave"):
         getattr(plan, name).restype = C.c_int64

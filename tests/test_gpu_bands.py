@@ -18,7 +18,7 @@ def _plan(n, sizes, tile):
     plan = plan_lib.load()
     t = [((w + tile - 1) // tile, (h + tile - 1) // tile) for w, h in sizes]
     rows = [min(plan.bin_rows(tx, max(ty for _, ty in t)), ty) for tx, ty in t]
-    return (plan.bin_chunk(n, sum(x * y for x, y in t), max(x * y for x, y in t)),
+    return (plan.bin_chunk(n, len(t), sum(x * y for x, y in t), max(x * y for x, y in t)),
             max(r * tx for r, (tx, _) in zip(rows, t)), max((ty + r - 1) // r for r, (_, ty) in zip(rows, t)))
 
 

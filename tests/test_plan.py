@@ -38,19 +38,20 @@ def test_pair_sum_grid(slots):
                                          (129_600, 1), (129_600, 4), (16_777_216, 1), (16_777_216, 256), (65, 64)])
 def test_binning_blocks(tiles, views):
     """Blocks grow before their number, the length of a column of the count
-    matrix, passes 256 or the matrix 2^20 entries, and no workspace has less
+    matrix, passes 256 (one view
+    in blocks of 1,024: 320) or the matrix 2^20 entries, and no workspace has less
     room than a smaller Gaussian count needs."""
     plan = plan_lib.load()
     room, largest = 0, (tiles + views - 1) // views
     for n in sorted([0, 1, 255, 256, 257, 4096, 30_011, 65_536, 65_537, 100_000, 131_073, 262_144, 300_007, 524_288, 524_289,
               1_000_000, 4_000_000, 100_000_000, LIMIT - 1] + list(range(2000, 6_000_000, 65_521))):
-        chunk = plan.bin_chunk(n, tiles, largest)
+        chunk = plan.bin_chunk(n, views, tiles, largest)
         blocks = plan.bin_blocks(n, chunk)
         assert blocks * chunk >= n and chunk % plan.bin_threads() == 0
         # a wave's share of a block is counted in 16 bits, and so is the block's
         assert 256 <= chunk <= 16384
         if n <= 256 * 2048 and tiles <= 4096:
-            assert blocks <= 256 and blocks * tiles <= 1 << 20
+            assert blocks <= (320 if chunk == 1024 and views == 1 else 256) and blocks * tiles <= 1 << 20
         assert blocks * largest <= 12 << 20 or chunk == 4096  # nor a view's part 12 x 2^20 in blocks of less than 4,096
         here = plan.bin_matrix_room(n, tiles, largest)
         assert blocks * tiles <= here and here >= room
