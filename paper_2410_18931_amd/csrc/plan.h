@@ -126,4 +126,20 @@ inline GridShape sum_grid(int64_t slots) {
   return {static_cast<uint32_t>(blocks < kRow ? blocks : kRow), static_cast<uint32_t>(rows), 1u};
 }
 
+// The loss of a launch's views in strips instead of tiles (see train.hip).  The
+// strips' time hardly depends on their number while every compute unit has at
+// most one, and then steps up; the tiles' grows with theirs.  Both passes, us,
+// tiles and strips: 640 x 705 (1,800 tiles, 210 strips) 48 / 53, four views of
+// 400 x 300 (1,900, 252) 51 / 53, 705 x 700 (1,980, 252) 61 / 53, 960 x 540
+// (2,040, 240) 58 / 53, 97 x 4700 (2,058, 278) 54 / 61, 800 x 720 (2,250, 286)
+// 59 / 61, 97 x 5700 (2,499, 336) 64 / 61, 1280 x 720 (3,600, 440) 84 / 64.
+// Views that fill their strips badly stay with tiles: lanes would idle, and the
+// workspace has room for the shares of the tiles.
+constexpr int32_t kLossTile = 16, kStripCols = 64, kStripRows = 34;
+constexpr int64_t kStripTiles = 1950, kStripTilesMore = 2300, kStripUnits = 256;
+constexpr bool loss_in_strips(int64_t tiles, int64_t strips, int64_t pixels) {
+  return tiles >= (strips <= kStripUnits ? kStripTiles : kStripTilesMore) &&
+         2 * kStripCols * kStripRows * strips <= 3 * pixels;
+}
+
 }  // namespace wsr

@@ -31,12 +31,14 @@
 // every SIMD some waves.  Both passes with the loss's sum, us, tiles and strips:
 // 17 x 9 and 65 x 33 14 / 49, 640 x 360 34 / 54, three views of 400 x 300
 // 43 / 55, 960 x 540 60 / 54, 1280 x 720 90 / 69, sixteen views of 400 x 300
-// 171 / 102, 1920 x 1080 209 / 108, four of them 719 / 400.
+// 171 / 102, 1920 x 1080 209 / 108, four of them 719 / 400.  Each launch of up to
+// 16 views takes the form that suits its views (loss_in_strips).
 #include <cmath>
 #include <type_traits>
 #include <mutex>
 
 #include "adam.h"
+#include "plan.h"
 #include "wsr_internal.h"
 
 // Workspace of the allocation-free loss entry point: the derivative maps and
@@ -50,13 +52,14 @@ static __device__ __align__(256) unsigned char scratch[WSR_LOSS_STATIC_BYTES];
 namespace wsr {
 namespace {
 
-constexpr int kLT = 16;               // output tile edge
+constexpr int kLT = kLossTile;        // output tile edge
 constexpr int kHalo = 5;              // window radius
 constexpr int kLE = kLT + 2 * kHalo;  // staged edge (26)
 constexpr int kTaps = 2 * kHalo + 1;
-constexpr int kStrip = kWave;         // output columns of a strip
-constexpr int kStripRows = 34;        // output rows: 44 staged rows, four rounds of eleven (23 rows: 130 us at
-                                      // 1920 x 1080 instead of 108, 45 rows: 116)
+constexpr int kStrip = kStripCols;    // output columns of a strip, one a lane; its kStripRows output rows take 44
+                                      // staged ones, four rounds of eleven (23 rows: 130 us at 1920 x 1080 instead
+                                      // of 108, 45 rows: 116)
+static_assert(kStrip == kWave, "a strip's columns are a wave's lanes");
 constexpr int kStaged = kStrip + 2 * kHalo;
 constexpr int kStripThreads = 3 * kWave;  // one wave per channel
 constexpr int kAhead = 3;             // rows loaded ahead (2: 116 us at 1920 x 1080, 3: 108, 4: 118, 5: 129)
@@ -552,14 +555,6 @@ int64_t loss_tiles(const wsr_camera* cams, int32_t nv, int w, int h) {
   return t;
 }
 
-// Strips from kStripPixels pixels on, where they are filled well (narrow views
-// would leave lanes idle, and have too little room for the shares, which the
-// workspace holds for 16 x 16 tiles).
-constexpr int64_t kStripPixels = 450000;
-bool use_strips(const wsr_camera* cams, int32_t nv, int64_t pixels) {
-  return pixels >= kStripPixels && 2 * kStrip * kStripRows * loss_tiles(cams, nv, kStrip, kStripRows) <= 3 * pixels;
-}
-
 int64_t loss_workspace_bytes(const wsr_camera* cams, int32_t nv) {
   int64_t pixels = 0;
   for (int v = 0; v < nv; ++v) pixels += static_cast<int64_t>(cams[v].width) * cams[v].height;
@@ -581,40 +576,44 @@ hipError_t launch_loss(const wsr_camera* cams, int32_t nv, const float* img, con
   a.dL = dL;
   a.total_pixels = pixels;
   a.lambda = lambda;
-  const bool strips = use_strips(cams, nv, pixels);
-  const int tw = strips ? kStrip : kLT, th = strips ? kStripRows : kLT;
+  int64_t pix_base = 0;
   int32_t tile0 = 0;
-  for (int pass = 1; pass <= 2; ++pass) {
-    int64_t pix_base = 0;
-    tile0 = 0;
-    for (int v0 = 0; v0 < nv; v0 += kLossViewsPerLaunch) {
-      LossViews lv = {};
-      gauss_taps(lv.gauss);
-      lv.nv = nv - v0 < kLossViewsPerLaunch ? nv - v0 : kLossViewsPerLaunch;
-      lv.tile0 = tile0;
-      int32_t tiles = 0;
-      for (int k = 0; k < lv.nv; ++k) {
-        const wsr_camera& c = cams[v0 + k];
-        lv.width[k] = c.width;
-        lv.height[k] = c.height;
-        lv.tiles_x[k] = (c.width + tw - 1) / tw;
-        lv.tile_base[k] = tiles;
-        lv.pix_base[k] = pix_base;
-        lv.scale[k] = static_cast<float>(1.0 / (3.0 * c.width * c.height * nv));
-        tiles += lv.tiles_x[k] * ((c.height + th - 1) / th);
-        pix_base += static_cast<int64_t>(c.width) * c.height;
-      }
-      lv.tile_base[lv.nv] = tiles;
-      tile0 += tiles;
-      if (tiles == 0) continue;
-      const unsigned count = static_cast<unsigned>(tiles);
-      if (strips && pass == 1) loss_strip_pass1<<<count, kStripThreads, 0, st>>>(a, lv);
-      else if (strips) loss_strip_pass2<<<count, kStripThreads, 0, st>>>(a, lv);
-      else if (pass == 1) loss_pass1<<<dim3(count, 3), 256, 0, st>>>(a, lv);
-      else loss_pass2<<<dim3(count, 3), 256, 0, st>>>(a, lv);
-      const hipError_t e = hipGetLastError();
-      if (e != hipSuccess) return e;
+  for (int v0 = 0; v0 < nv; v0 += kLossViewsPerLaunch) {
+    LossViews lv = {};
+    gauss_taps(lv.gauss);
+    lv.nv = nv - v0 < kLossViewsPerLaunch ? nv - v0 : kLossViewsPerLaunch;
+    lv.tile0 = tile0;
+    const wsr_camera* c = cams + v0;
+    int64_t here = 0;
+    for (int k = 0; k < lv.nv; ++k) here += static_cast<int64_t>(c[k].width) * c[k].height;
+    const bool strips = loss_in_strips(loss_tiles(c, lv.nv, kLT, kLT), loss_tiles(c, lv.nv, kStrip, kStripRows), here);
+    const int tw = strips ? kStrip : kLT, th = strips ? kStripRows : kLT;
+    int32_t tiles = 0;
+    for (int k = 0; k < lv.nv; ++k) {
+      lv.width[k] = c[k].width;
+      lv.height[k] = c[k].height;
+      lv.tiles_x[k] = (c[k].width + tw - 1) / tw;
+      lv.tile_base[k] = tiles;
+      lv.pix_base[k] = pix_base;
+      lv.scale[k] = static_cast<float>(1.0 / (3.0 * c[k].width * c[k].height * nv));
+      tiles += lv.tiles_x[k] * ((c[k].height + th - 1) / th);
+      pix_base += static_cast<int64_t>(c[k].width) * c[k].height;
     }
+    lv.tile_base[lv.nv] = tiles;
+    tile0 += tiles;
+    if (tiles == 0) continue;
+    // both passes of these views before the next ones, whose maps may lie
+    // otherwise in the same workspace
+    const unsigned count = static_cast<unsigned>(tiles);
+    if (strips) {
+      loss_strip_pass1<<<count, kStripThreads, 0, st>>>(a, lv);
+      loss_strip_pass2<<<count, kStripThreads, 0, st>>>(a, lv);
+    } else {
+      loss_pass1<<<dim3(count, 3), 256, 0, st>>>(a, lv);
+      loss_pass2<<<dim3(count, 3), 256, 0, st>>>(a, lv);
+    }
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
   }
   loss_finalize<<<1, 256, 0, st>>>(a.part, static_cast<int64_t>(tile0) * 3, loss);
   return hipGetLastError();

@@ -38,6 +38,9 @@ int64_t shared_tags(int64_t width, int64_t pitch) {
   return shared;
 }
 int64_t bin_rows(int64_t tiles_x, int64_t max_tiles_y) { return wsr::bin_rows(tiles_x, max_tiles_y); }
+int64_t loss_in_strips(int64_t tiles, int64_t strips, int64_t pixels) {
+  return wsr::loss_in_strips(tiles, strips, pixels);
+}
 int64_t few_tiles() { return wsr::kFewTiles; }
 int64_t bin_threads() { return wsr::kBinThreads; }
 int64_t sum_waves() { return wsr::kSumWaves; }
@@ -55,8 +58,8 @@ def load():
     subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-fPIC", "-shared", "-I",
                     os.path.join(ROOT, "paper_2410_18931_amd", "csrc"), src, "-o", lib], check=True)
     plan = C.CDLL(lib)
-    for name in ("bin_blocks", "bin_rows", "shared_tags", "bin_chunk", "bin_matrix_room"):
-        getattr(plan, name).argtypes = [C.c_int64] * {"bin_chunk": 4, "bin_matrix_room": 3}.get(name, 2)
+    for name in ("bin_blocks", "bin_rows", "shared_tags", "bin_chunk", "bin_matrix_room", "loss_in_strips"):
+        getattr(plan, name).argtypes = [C.c_int64] * {"bin_chunk": 4, "bin_matrix_room": 3, "loss_in_strips": 3}.get(name, 2)
         getattr(plan, name).restype = C.c_int64
     for name in ("bin_tag_pitch", "bin_threads", "few_tiles", "sum_waves", "sum_per_wave"):
         getattr(plan, name).restype = C.c_int64
@@ -70,3 +73,14 @@ def grid(name, *args):
     g = (C.c_int64 * 3)()
     getattr(load(), name)(*args, g)
     return tuple(g)
+
+
+def loss_forms(sizes):
+    """Form of the loss of each launch of up to 16 views: strips or tiles."""
+    out = []
+    for k in range(0, len(sizes), 16):
+        views = sizes[k:k + 16]
+        cut = lambda a, b: sum(-(-w // a) * -(-h // b) for w, h in views)  # noqa: E731
+        strips = load().loss_in_strips(cut(16, 16), cut(64, 34), sum(w * h for w, h in views))
+        out.append("strips" if strips else "tiles")
+    return out

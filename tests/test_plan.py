@@ -83,3 +83,25 @@ def test_binning_bands(views):
         rows = plan.bin_rows(tx, tallest)
         assert rows >= 1 and 12 * rows * tx + 5136 <= 65536
         assert rows == (tallest + 5) // 6 or (rows + 1) * tx > 4864
+
+
+@pytest.mark.parametrize("sizes,forms", [
+    ([(17, 9)], ["tiles"]), ([(640, 360)], ["tiles"]), ([(640, 705)], ["tiles"]), ([(400, 300)] * 4, ["tiles"]),
+    ([(705, 700)], ["strips"]), ([(960, 540)], ["strips"]), ([(97, 4700)], ["tiles"]), ([(800, 720)], ["tiles"]),
+    ([(1280, 720)], ["strips"]), ([(1920, 1080)], ["strips"]), ([(400, 300)] * 16, ["strips"]),
+    # many small views: what one launch holds decides, not all pixels
+    ([(300, 100)] * 17, ["strips", "tiles"]), ([(128, 128)] * 28, ["tiles"] * 2), ([(64, 64)] * 130, ["tiles"] * 9),
+    ([(64, 64)] * 256, ["tiles"] * 16), ([(1920, 1080)] + [(64, 64)] * 16, ["strips", "tiles"]),
+    # strips badly filled
+    ([(65, 20_000)], ["tiles"]), ([(32_767, 20)], ["tiles"])])
+def test_form_of_the_loss(sizes, forms):
+    assert plan_lib.loss_forms(sizes) == forms
+
+
+def test_shares_of_strips_fit_the_room_of_tiles():
+    """The workspace holds one share per 16 x 16 tile and channel; strips are
+    taken only where they are fewer, whatever the views' sizes."""
+    for w in list(range(1, 70)) + [127, 128, 129, 255, 700, 1920, 32_767]:
+        for h in [1, 2, 33, 34, 35, 68, 69, 500, 5000, 32_767]:
+            tiles, strips = -(-w // 16) * -(-h // 16), -(-w // 64) * -(-h // 34)
+            assert not plan_lib.load().loss_in_strips(tiles, strips, w * h) or strips <= tiles
