@@ -159,6 +159,41 @@ __device__ __forceinline__ double block_sum_256(double x, double* sh) {
   return t;
 }
 
+// The map at a pixel and its derivatives, from the windowed statistics.  Every
+// fused operation is written out and none is left to the compiler, so that tiles
+// and strips give the same bits.
+struct SsimTerm {
+  float s, d_u, d_sxx, d_sxy;
+};
+__device__ __forceinline__ SsimTerm ssim_term(float u, float v, float sxx, float syy, float sxy) {
+#pragma clang fp contract(off)
+  const float u2 = u + u, v2 = v + v;
+  const float a1 = fmaf(v, u2, kC1);
+  const float a2 = fmaf(2.f, fmaf(-v, u, sxy), kC2);
+  const float b1 = fmaf(v, v, u * u) + kC1;
+  const float b2 = (fmaf(-v, v, syy) + fmaf(-u, u, sxx)) + kC2;
+  const float ib = 1.f / (b1 * b2);
+  SsimTerm t;
+  t.s = a1 * a2 * ib;
+  t.d_u = fmaf(fmaf(v2, a2, -(v2 * a1)), ib, (u2 / b1 - u2 / b2) * -t.s);
+  t.d_sxx = -t.s / b2;
+  t.d_sxy = (a1 + a1) * ib;
+  return t;
+}
+
+// An entry's part of L_v V P_v: (1 - lambda)|x - y| + lambda (1 - S).
+__device__ __forceinline__ double loss_share(float x, float y, float s, float lambda) {
+  return (1.0 - lambda) * fabs(static_cast<double>(x) - y) + lambda * (1.0 - static_cast<double>(s));
+}
+
+// dL/dx of an entry from the filtered derivative maps f (see ssim_term).
+__device__ __forceinline__ float loss_grad(float x, float y, float f0, float f1, float f2, float lambda, float scale) {
+#pragma clang fp contract(off)
+  const float sgn = x > y ? 1.f : (x < y ? -1.f : 0.f);
+  const float dmean = fmaf(y, f2, fmaf(x + x, f1, f0));
+  return scale * fmaf(1.f - lambda, sgn, -(lambda * dmean));
+}
+
 __global__ __launch_bounds__(256) void loss_pass1(LossArgs a, LossViews lv) {
   __shared__ float2 s_xy[kLE][kLE + 1];   // (x, y)
   __shared__ float4 s_h4[kLE][kLT + 1];   // row-filtered x, y, x^2, y^2
@@ -207,23 +242,14 @@ __global__ __launch_bounds__(256) void loss_pass1(LossArgs a, LossViews lv) {
       syy = fmaf(gq, h.w, syy);
       sxy = fmaf(gq, h1, sxy);
     }
-    const float a1 = 2.f * u * v + kC1;
-    const float a2 = 2.f * (sxy - u * v) + kC2;
-    const float b1 = u * u + v * v + kC1;
-    const float b2 = (sxx - u * u) + (syy - v * v) + kC2;
-    const float ib = 1.f / (b1 * b2);
-    const float s = a1 * a2 * ib;
-    const float d_u = (2.f * v * a2 - 2.f * v * a1) * ib - s * (2.f * u / b1 - 2.f * u / b2);
-    const float d_sxx = -s / b2;
-    const float d_sxy = 2.f * a1 * ib;
+    const SsimTerm m = ssim_term(u, v, sxx, syy, sxy);
     const int64_t pix = lv.pix_base[w.v] + static_cast<int64_t>(py) * lv.width[w.v] + px;
     const int64_t P = a.total_pixels;
-    a.dmaps[(0 * 3 + ch) * P + pix] = d_u;
-    a.dmaps[(1 * 3 + ch) * P + pix] = d_sxx;
-    a.dmaps[(2 * 3 + ch) * P + pix] = d_sxy;
+    a.dmaps[(0 * 3 + ch) * P + pix] = m.d_u;
+    a.dmaps[(1 * 3 + ch) * P + pix] = m.d_sxx;
+    a.dmaps[(2 * 3 + ch) * P + pix] = m.d_sxy;
     const float x = s_xy[i + kHalo][j + kHalo].x, y = s_xy[i + kHalo][j + kHalo].y;
-    // this entry's part of L_v * V * P_v: (1 - lambda)|x - y| + lambda (1 - S)
-    share = (1.0 - a.lambda) * fabs(static_cast<double>(x) - y) + a.lambda * (1.0 - static_cast<double>(s));
+    share = loss_share(x, y, m.s, a.lambda);
   }
   share = block_sum_256(share, s_red);
   if (threadIdx.x == 0) a.part[static_cast<int64_t>(lv.tile0 + t) * 3 + ch] = share * lv.scale[w.v];
@@ -268,10 +294,7 @@ __global__ __launch_bounds__(256) void loss_pass2(LossArgs a, LossViews lv) {
   if (px >= lv.width[w.v] || py >= lv.height[w.v]) return;
   const int64_t pix = lv.pix_base[w.v] + static_cast<int64_t>(py) * lv.width[w.v] + px;
   const float x = a.img[3 * pix + ch], y = a.target[3 * pix + ch];
-  const float sgn = x > y ? 1.f : (x < y ? -1.f : 0.f);
-  const float dmean = f[0] + 2.f * x * f[1] + y * f[2];
-  const float sc = lv.scale[w.v];
-  a.dL[3 * pix + ch] = sc * ((1.f - a.lambda) * sgn - a.lambda * dmean);
+  a.dL[3 * pix + ch] = loss_grad(x, y, f[0], f[1], f[2], a.lambda, lv.scale[w.v]);
 }
 
 // Where a strip lies, and the lane's part of a staged row: its own pixel at
@@ -395,25 +418,13 @@ __global__ __launch_bounds__(kStripThreads, 4) void loss_strip_pass1(LossArgs a,
         syy = fmaf(g[q], hyy[r], syy);
         sxy = fmaf(g[q], hxy[r], sxy);
       }
-      // the map and its derivatives, written out with the fused operations that
-      // the compiler forms in loss_pass1, so that both give the same bits
-      const float u2 = u + u, v2 = v + v;
-      const float a1 = fmaf(v, u2, kC1);
-      const float a2 = fmaf(2.f, fmaf(-v, u, sxy), kC2);
-      const float b1 = fmaf(v, v, u * u) + kC1;
-      const float b2 = (fmaf(-v, v, syy) + fmaf(-u, u, sxx)) + kC2;
-      const float ib = 1.f / (b1 * b2);
-      const float s = a1 * a2 * ib;
-      const float d_u = fmaf(fmaf(v2, a2, -(v2 * a1)), ib, (u2 / b1 - u2 / b2) * -s);
-      const float d_sxx = -s / b2;
-      const float d_sxy = (a1 + a1) * ib;
+      const SsimTerm m = ssim_term(u, v, sxx, syy, sxy);
       if (out_col) {
         const int64_t at = ch * a.total_pixels + w.pix_base + static_cast<int64_t>(oy) * w.width + w.x0;
-        (a.dmap2 + at)[lane] = make_float2(d_u, d_sxx);
-        (a.dmap1 + at)[lane] = d_sxy;
-        // this entry's part of L_v * V * P_v: (1 - lambda)|x - y| + lambda (1 - S)
+        (a.dmap2 + at)[lane] = make_float2(m.d_u, m.d_sxx);
+        (a.dmap1 + at)[lane] = m.d_sxy;
         const float x = cx[(k + 1 + kHalo) % kTaps], y = cy[(k + 1 + kHalo) % kTaps];
-        share += (1.0 - a.lambda) * fabs(static_cast<double>(x) - y) + a.lambda * (1.0 - static_cast<double>(s));
+        share += loss_share(x, y, m.s, a.lambda);
       }
     }
   }
@@ -492,10 +503,7 @@ __global__ __launch_bounds__(kStripThreads, 4) void loss_strip_pass2(LossArgs a,
         f1 = fmaf(g[q], h1[r], f1);
         f2 = fmaf(g[q], h2[r], f2);
       }
-      const float x = l.x, y = l.y;
-      const float sgn = x > y ? 1.f : (x < y ? -1.f : 0.f);
-      const float dmean = f0 + 2.f * x * f1 + y * f2;
-      s_out[k][3 * lane + ch] = sc * ((1.f - lambda) * sgn - lambda * dmean);
+      s_out[k][3 * lane + ch] = loss_grad(l.x, l.y, f0, f1, f2, lambda, sc);
     }
     __syncthreads();
     const int t = static_cast<int>(threadIdx.x);

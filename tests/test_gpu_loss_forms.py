@@ -41,3 +41,26 @@ def test_loss_of_each_form(sizes, forms):
         err = np.abs(got[at:at + w * h] - g.reshape(-1, 3)).max()
         at += w * h
         assert err <= DL_TOL * np.abs(g).max(), (w, h, err)
+
+
+@pytest.mark.parametrize("size,copies", [((800, 600), 2), ((703, 341), 4), ((130, 777), 8), ((64, 1020), 8)])
+def test_strips_give_the_tiles_bits(size, copies):
+    """A view alone takes tiles, a power of two of copies of it strips: each
+    copy's gradient is the view's, divided by their number, to the bit."""
+    w, h = size
+    log(f"case: loss bits {size} x {copies}")
+    assert plan_lib.loss_forms([size]) == ["tiles"] and plan_lib.loss_forms([size] * copies) == ["strips"]
+    rng = np.random.default_rng(w)
+    img = rng.random((h, w, 3)).astype(np.float32)
+    tgt = np.clip(img + rng.normal(0, 0.1, img.shape), 0, 1).astype(np.float32)
+    img[: h // 4] = tgt[: h // 4]           # equal, dark and bright parts
+    img[h // 4: h // 3, : w // 2] = tgt[h // 4: h // 3, : w // 2] = 0.0
+    img[h // 2: h // 2 + 40] *= 30.0
+    a, b = (torch.from_numpy(x.reshape(-1, 3)).cuda() for x in (img, tgt))
+    one, dL_one = Loss(_cams([size]))(a, b)
+    many, dL = Loss(_cams([size] * copies))(a.repeat(copies, 1), b.repeat(copies, 1))
+    torch.cuda.synchronize()
+    for k in range(copies):
+        assert torch.equal(copies * dL[k * w * h:(k + 1) * w * h], dL_one), k
+    # the shares are summed in FP64 in another order
+    assert abs(many.item() - one.item()) <= 2.0 ** -22 * abs(one.item())
