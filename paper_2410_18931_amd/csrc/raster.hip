@@ -1709,13 +1709,15 @@ hipError_t launch_sort_tiles(const Layout& L, void* ws, void* pairs, int64_t cap
                                                                              slots, queue.head);
   sort_short_kernel<<<static_cast<unsigned>(L.total_tiles), kSortThreads, 0, st>>>(
       cams, L.nv, depths, L.n, at<uint4>(ws, L.off_torder), static_cast<uint32_t>(capacity), pv.ent, queue, flags);
-  // as many workgroups as run at once, and no more than there can be lists
+  // one workgroup runs on a compute unit (96 and 144 KB of LDS each), so as many
+  // as there are units, and no more than there can be lists
+  const int64_t units = std::min<int64_t>(256, L.total_tiles);
   if (capacity > kSortSmall)
-    sort_long_kernel<kSortMid><<<static_cast<unsigned>(std::min<int64_t>({512, L.total_tiles, capacity / kSortSmall})),
-                                 1024, 0, st>>>(cams, L.nv, depths, L.n, tstart, capacity, pv.ent, queue);
+    sort_long_kernel<kSortMid><<<static_cast<unsigned>(std::min(units, capacity / kSortSmall)), 1024, 0, st>>>(
+        cams, L.nv, depths, L.n, tstart, capacity, pv.ent, queue);
   if (capacity > kSortMid)
-    sort_long_kernel<kSortMax><<<static_cast<unsigned>(std::min<int64_t>({256, L.total_tiles, capacity / kSortMid})),
-                                 1024, 0, st>>>(cams, L.nv, depths, L.n, tstart, capacity, pv.ent, queue);
+    sort_long_kernel<kSortMax><<<static_cast<unsigned>(std::min(units, capacity / kSortMid)), 1024, 0, st>>>(
+        cams, L.nv, depths, L.n, tstart, capacity, pv.ent, queue);
   return hipGetLastError();
 }
 
