@@ -128,8 +128,6 @@ bool make_layout(int64_t n, const wsr_camera* cams, int32_t nv, int32_t tile, La
   }
   L->total_tiles = tiles;
   L->total_pixels = pixels;
-  L->hist_len = hist;
-  L->scan_parts = static_cast<int64_t>(nv) * L->nblk;  // one rectangle sum per (view, binning block)
   L->gpart_blocks = project_bwd_blocks(n);
   const int64_t slots = n * nv;
   size_t off = 0;
