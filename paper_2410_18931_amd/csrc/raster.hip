@@ -1160,11 +1160,11 @@ __device__ __forceinline__ void lds_barrier() {
 // to a CU, and leaves the longer ones to two kernels with more shared memory.
 // More buckets pay where the shared memory allows them: depths come in clumps,
 // and the comparisons are most of the work (lists of 2,049 to 8,192 entries
-// with 2,048, 4,096 and 8,192 buckets: 84, 67 and 63 us; up to 2,048 entries
-// with 2,048 and 1,024, which lets two more workgroups share a CU: 65 and
-// 62 us).  All lists of 1 M Gaussians at 1080p: 596 us with bitonic networks
-// throughout (66 barriers for 2,048 entries), 133 us now, of which the dense
-// depths take 11 and save 31.
+// with 2,048, 4,096 and 8,192 buckets: 84, 67 and 63 us, one workgroup to a CU
+// in the last two; up to 2,048 entries with 2,048 and 1,024, which lets two more
+// workgroups share a CU: 65 and 62 us).  All lists of 1 M Gaussians at 1080p:
+// 596 us with bitonic networks throughout (66 barriers for 2,048 entries),
+// 131 us now, of which the dense depths take 11 and save 31.
 constexpr int kSortSmall = kItemSplats;
 constexpr int kSortMid = 8192;
 constexpr uint32_t kSortCrowd = 64;
@@ -1459,8 +1459,8 @@ __global__ __launch_bounds__(TileGeom<T>::kThreads) void raster_sorted_kernel(Ra
       }
     };
     // four layers per step: their records and alphas do not depend on the
-    // transmittance, so their latencies are paid once (1 M Gaussians / 1080p,
-    // sorting and composition: 285 us one by one, 252 so)
+    // transmittance, so their latencies are paid once (1 M Gaussians / 1080p:
+    // 152 us one by one, 130 so)
     int i = 0;
     for (; i + 4 <= m && __any(live); i += 4) {
       const uint32_t four = *reinterpret_cast<const uint32_t*>(list + i);
