@@ -272,8 +272,13 @@ __device__ __forceinline__ void tile_setup(const RasterArgs& a, uint32_t item, T
     s0 = d.y;
     e0 = d.z;
   }
-  s0 = min(s0, cap);
-  e0 = max(min(e0, cap), s0);
+  // the same for the whole workgroup: in scalar registers, as vector registers
+  // decide how many waves run
+  c.tile = __builtin_amdgcn_readfirstlane(static_cast<int>(c.tile));
+  c.k = __builtin_amdgcn_readfirstlane(c.k);
+  c.nk = __builtin_amdgcn_readfirstlane(c.nk);
+  s0 = min(static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(s0)), cap);
+  e0 = max(min(static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(e0)), cap), s0);
   const int tile = static_cast<int>(c.tile);
   c.v = find_view(a.cams, a.nv, tile);
   cam = &a.cams[c.v];
