@@ -29,11 +29,12 @@ struct GridShape {
 // the chip idle, and up to kBinBlocksFull blocks of 1,024 are better (300 k at
 // 1001 x 747, 293 blocks: 53.2 us and 55.4 in blocks of 2,048).
 //
-// Where a view's part of the matrix has more than kBinLarge entries even so, what a block does for
-// every tile (its counts, their prefix sums, its row of the matrix) is most of
-// the stage, and blocks of 4,096 halve it: 1 M Gaussians at 3840 x 2160 and tiles
-// 16 and 8 386 -> 340 and 1,466 -> 1,117 us (372 and 1,907 before rectangles were
-// counted by their corners), at 7680 x 4320 and tile 16 1,470 -> 1,113 us.
+// Where a view's part of the matrix has more than kBinLarge entries even so, what
+// a block does for every tile (its counts, their prefix sums, its row of the
+// matrix) is most of the stage, and blocks of 4,096 halve it: 1 M Gaussians at
+// 3840 x 2160 and tiles 16 and 8 386 -> 340 and 1,466 -> 1,117 us (372 and 1,907
+// before rectangles were counted by their corners), at 7680 x 4320 and tile 16
+// 1,470 -> 1,113 us.
 constexpr int32_t kBinChunkMin = 256, kBinChunkMax = 2048, kBinChunkLarge = 4096;
 constexpr int64_t kBinSmall = 1 << 20, kBinLarge = 12 << 20, kBinBlocks = 256, kBinBlocksFull = 320;
 
@@ -94,11 +95,12 @@ constexpr int32_t kFewBits = 5, kFewTiles = 1 << kFewBits;
 // lies k pitches further on, modulo the number of tags, and as both are in the
 // step only if a row has fewer than 64 / (k - 1) tiles, as many tags between them
 // are enough.  The pitch is the view's width where that holds, which spreads a
-// band's tiles best, and else the next larger one where it does.  Among the widths where it does not hold are the powers of two
-// (1 M Gaussians, the stage at 2048 x 1024 and tile 8, 4096 x 2160 and tiles 16
-// and 8, 8192 x 4320 and tile 8: 443, 481, 2,472 and 10,451 us with tags by width,
-// 328, 353, 1,147 and 4,784 now).  A pitch of 67 throughout costs 149 instead of
-// 142 us at 1080p, where a band's 12 rows of 120 tiles then share 857 tags.
+// band's tiles best, and else the next larger one where it does.  Among the widths
+// where it does not hold are the powers of two (1 M Gaussians, the stage at
+// 2048 x 1024 and tile 8, 4096 x 2160 and tiles 16 and 8, 8192 x 4320 and tile 8:
+// 443, 481, 2,472 and 10,451 us with tags by width, 328, 353, 1,147 and 4,784 now).
+// A pitch of 67 throughout costs 149 instead of 142 us at 1080p, where a band's 12
+// rows of 120 tiles then share 857 tags.
 constexpr uint32_t kTags = 1024;
 constexpr uint32_t bin_tag(uint32_t row, uint32_t col, uint32_t pitch) { return (row * pitch + col) % kTags; }
 
@@ -106,7 +108,8 @@ inline int32_t bin_tag_pitch(int32_t tiles_x) {
   auto apart = [&](int32_t pitch) {
     for (int32_t k = 1; k < 64; ++k) {
       const int32_t far = k * pitch % static_cast<int32_t>(kTags);
-      if (std::min(far, static_cast<int32_t>(kTags) - far) < std::min(tiles_x, k == 1 ? 64 : 63 / (k - 1))) return false;
+      const int32_t gap = std::min(far, static_cast<int32_t>(kTags) - far);
+      if (gap < std::min(tiles_x, k == 1 ? 64 : 63 / (k - 1))) return false;
     }
     return true;
   };

@@ -383,10 +383,11 @@ __global__ __launch_bounds__(kBwdBlock) void project_bwd_kernel(BwdArgs a) {
 // share a Gaussian, one float3 of the nine floats each, so that a load touches
 // a cache line or two per Gaussian for all 36 bytes instead of one for every
 // 12 (1 M Gaussians / 1080p, this kernel and the chain below: 273 us with a lane
-// per Gaussian, 261 now; sixteen views 1,455 and 1,406).  A long range (a splat covering many tiles) is summed by the whole
-// wave, lanes striding through it, so the largest splats do not form a serial
-// tail.  With OIT (DU) the same pass also sums each pair's dL/du through the
-// coverage term, which the raster stores in an array of its own.
+// per Gaussian, 261 now; sixteen views 1,455 and 1,406).  A long range (a splat
+// covering many tiles) is summed by the whole wave, lanes striding through it,
+// so the largest splats do not form a serial tail.  With OIT (DU) the same pass
+// also sums each pair's dL/du through the coverage term, which the raster stores
+// in an array of its own.
 constexpr uint32_t kHeavySlots = 32;
 constexpr uint32_t kSumStep = 4;         // loads in flight per lane (6 and 8: 269 and 263 us instead of 261)
 
